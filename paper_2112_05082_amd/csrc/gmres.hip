@@ -35,6 +35,14 @@ constexpr int kFoldMaxVec = 16;
 // The element-parallel update (long vectors) keeps one element's entries of
 // every basis vector and folds steps of up to 32 vectors.
 constexpr int kFoldMaxVecEl = 32;
+// Partials per Gram-Schmidt coefficient that the update's blocks sum
+// themselves, of the inner products' chunks (a load per lane) and of a folded
+// update's blocks (two loads); above, a launch of its own sums them once.
+constexpr int kPartialsInUpdate = 64;
+constexpr int kPartials2InUpdate = 128;
+// longest vector of the batch from which the updates run element-parallel,
+// by basis type (see update_runs)
+constexpr int64_t kElementMin32 = 8192, kElementMin64 = 16384;
 constexpr int kCheckEvery = 4;
 
 struct RhsVec {
@@ -239,24 +247,79 @@ __device__ void givens_step_block(int b, double2* __restrict__ H, double2* __res
 }
 
 // Sum of n partials by the 64 lanes of one wave: lane t adds entries t, t+64,
-// ... in order, then a fixed butterfly; every lane returns the total.
-__device__ double wave_sum_partials(const volatile double* p, int n) {
+// ... in order (four loads in flight), then a fixed butterfly; every lane
+// returns the total.
+__device__ double wave_sum_partials(const double* p, int n) {
   double acc = 0.0;
-  for (int q = (int)(threadIdx.x & 63); q < n; q += 64) acc += p[q];
+  for (int q0 = (int)(threadIdx.x & 63); q0 < n; q0 += 256) {
+    double v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = q0 + 64 * u < n ? p[q0 + 64 * u] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc += v[u];
+  }
   for (int o = 32; o >= 1; o >>= 1) acc += __shfl_xor(acc, o);
   return acc;
 }
-__device__ double2 wave_sum_partials2(const volatile double2* p, int n) {
+// up to this many complex partials are added one by one by a single thread
+constexpr int kSerialPartials = 8;
+__device__ double2 serial_sum_partials2(const double2* p, int n) {
   double2 acc = make_double2(0.0, 0.0);
-  for (int q = (int)(threadIdx.x & 63); q < n; q += 64) {
+  for (int q = 0; q < n; ++q) {
     acc.x += p[q].x;
     acc.y += p[q].y;
+  }
+  return acc;
+}
+__device__ double2 wave_sum_partials2(const double2* p, int n) {
+  if (n <= kSerialPartials) return serial_sum_partials2(p, n);
+  double2 acc = make_double2(0.0, 0.0);
+  for (int q0 = (int)(threadIdx.x & 63); q0 < n; q0 += 256) {
+    double2 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = q0 + 64 * u < n ? p[q0 + 64 * u] : make_double2(0.0, 0.0);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      acc.x += v[u].x;
+      acc.y += v[u].y;
+    }
   }
   for (int o = 32; o >= 1; o >>= 1) {
     acc.x += __shfl_xor(acc.x, o);
     acc.y += __shfl_xor(acc.y, o);
   }
   return acc;
+}
+
+// Gram-Schmidt coefficients of one right-hand side in a 256-thread block:
+// hb[i] = the sum of the P partials partial[i maxP ...], and (h non-null) its
+// record in column j of H (h = &H[0][j], rows m apart; mode 0 stores, 1 adds).
+// A wave sums one vector's partials at a time with all its lanes (one thread
+// per vector adds them one by one: at 640 partials the update of 24 right-hand
+// sides of 40,960 took 250 us that way).  The order is that of
+// finish_partials_kernel, so a coefficient does not depend on which of the
+// two sums it.
+__device__ void sum_coefficients(const double2* partial, int maxP, int P, int nvec, double2* hb, double2* h, int m,
+                                 int mode) {
+  auto record = [&](int i, double2 t) {
+    hb[i] = t;
+    if (!h) return;
+    double2* hi = h + (size_t)i * m;
+    if (mode == 0) {
+      *hi = t;
+    } else {
+      hi->x += t.x;
+      hi->y += t.y;
+    }
+  };
+  if (P <= kSerialPartials) {
+    for (int i = threadIdx.x; i < nvec; i += blockDim.x) record(i, serial_sum_partials2(partial + (size_t)i * maxP, P));
+  } else {
+    for (int i = threadIdx.x >> 6; i < nvec; i += 4) {
+      const double2 t = wave_sum_partials2(partial + (size_t)i * maxP, P);
+      if ((threadIdx.x & 63) == 0) record(i, t);
+    }
+  }
 }
 
 // Block sum of a double2 over the 256 threads (fixed order).
@@ -399,27 +462,22 @@ dots_partials_kernel(const VB* __restrict__ A, int64_t a_stride, const WB* __res
   }
 }
 
-// Long vectors: the partials of dots_partials_kernel (one per part_chunk
-// elements) or of the folded update (one per update block) summed once, in a
-// fixed order, into out[b][i] (grid (nvec, B)), so that the update kernel's
-// blocks read one value per vector instead of every partial.
+// Many partials per vector (see kPartialsInUpdate): the partials of
+// dots_partials_kernel (one per part_chunk elements) or of the folded update
+// (one per update block) summed once, in a fixed order, into out[b][i], so
+// that the update kernel's blocks read one value per vector instead of every
+// partial.  Grid (ceil(nvec / 4), B), one wave per vector.
 __global__ void __launch_bounds__(256)
 finish_partials_kernel(const double2* __restrict__ partial, int maxP, int nvec, const RhsVec* __restrict__ rv,
                        double2* __restrict__ out, const int* __restrict__ run_prev, const int* __restrict__ idle,
                        int part_chunk) {
   if (run_prev && *run_prev == 0) return;
   if (idle && idle[blockIdx.y]) return;
-  __shared__ double2 sh[4];
-  const int i = blockIdx.x, b = blockIdx.y;
-  const int64_t P = (rv[b].N + part_chunk - 1) / part_chunk;
-  const double2* pp = partial + ((size_t)b * nvec + i) * maxP;
-  double2 t = make_double2(0.0, 0.0);
-  for (int64_t p = threadIdx.x; p < P; p += blockDim.x) {
-    t.x += pp[p].x;
-    t.y += pp[p].y;
-  }
-  t = block_sum2(t, sh);
-  if (threadIdx.x == 0) out[(size_t)b * nvec + i] = t;
+  const int i = blockIdx.x * 4 + (threadIdx.x >> 6), b = blockIdx.y;
+  if (i >= nvec) return;
+  const int P = (int)((rv[b].N + part_chunk - 1) / part_chunk);
+  const double2 t = wave_sum_partials2(partial + ((size_t)b * nvec + i) * maxP, P);
+  if ((threadIdx.x & 63) == 0) out[(size_t)b * nvec + i] = t;
 }
 
 // the per-block parts of ||w||^2 summed once into out[b] (grid B)
@@ -478,25 +536,8 @@ gs_update_kernel(const VB* __restrict__ V, WB* __restrict__ w, const RhsVec* __r
     if (blk >= nb) continue;
     const int P = n_part > 0 ? n_part : (int)((r.N + part_chunk - 1) / part_chunk);
     __syncthreads();  // the previous item's reads of hb are done
-    for (int i = threadIdx.x; i < nvec; i += blockDim.x) {
-      const double2* pp = partial + ((size_t)b * nvec + i) * maxP;
-      double2 t = make_double2(0.0, 0.0);
-      for (int p = 0; p < P; ++p) {
-        const double2 v = pp[p];
-        t.x += v.x;
-        t.y += v.y;
-      }
-      hb[i] = t;
-      if (blk == 0) {
-        double2* h = H + (size_t)b * (m + 1) * m + (size_t)i * m + j;
-        if (mode == 0) {
-          *h = t;
-        } else {
-          h->x += t.x;
-          h->y += t.y;
-        }
-      }
-    }
+    sum_coefficients(partial + (size_t)b * nvec * maxP, maxP, P, nvec, hb,
+                     blk == 0 ? H + (size_t)b * (m + 1) * m + j : nullptr, m, mode);
     __syncthreads();
     const bool act = st[b].active;
     double nrm2 = 0.0;
@@ -662,25 +703,8 @@ gs_update_el_kernel(const VB* __restrict__ V, WB* __restrict__ w, const RhsVec* 
         if (i < nvec) vv[i] = vk[(int64_t)i * ut];
     }
     __syncthreads();  // the previous item's reads of hb and red are done
-    for (int i = tid; i < nvec; i += blockDim.x) {
-      const double2* pp = partial + ((size_t)b * nvec + i) * maxP;
-      double2 t = make_double2(0.0, 0.0);
-      for (int p = 0; p < P; ++p) {
-        const double2 v = pp[p];
-        t.x += v.x;
-        t.y += v.y;
-      }
-      hb[i] = t;
-      if (blk == 0) {
-        double2* h = H + (size_t)b * (m + 1) * m + (size_t)i * m + j;
-        if (mode == 0) {
-          *h = t;
-        } else {
-          h->x += t.x;
-          h->y += t.y;
-        }
-      }
-    }
+    sum_coefficients(partial + (size_t)b * nvec * maxP, maxP, P, nvec, hb,
+                     blk == 0 ? H + (size_t)b * (m + 1) * m + j : nullptr, m, mode);
     __syncthreads();
     double nrm2 = 0.0;
     if (live) {
@@ -766,8 +790,8 @@ bool selective_cgs2() {
   return sel;
 }
 
-// ||w|| from the per-block parts of the preceding gs_update_kernel (n_npart
-// of them; 0: one per 64 elements), summed by every block in the same fixed
+// ||w|| from the per-block parts of the preceding update (one per part_el
+// elements; 0: one in all), summed by every block in the same fixed
 // order; block 0 sets H[j+1][j] = ||w|| and
 // applies the Givens step; every block writes V_{j+1} = w / ||w|| (zeros for
 // a finished RHS or a breakdown) and, for the next step's matvec, its input
@@ -782,7 +806,7 @@ bool selective_cgs2() {
 template <typename OT, int MODE, typename VB, typename WB, int RW = 1>
 __global__ void __launch_bounds__(256)
 normalize_step_kernel(const WB* __restrict__ w, VB* __restrict__ V, const RhsVec* __restrict__ rv,
-                      RhsState* __restrict__ st, const double* __restrict__ npart, int maxB, int n_npart,
+                      RhsState* __restrict__ st, const double* __restrict__ npart, int maxB, int part_el,
                       double2* __restrict__ H, double2* __restrict__ g, double* __restrict__ cs,
                       double2* __restrict__ sn, int m, int j, double tol, int* __restrict__ n_running,
                       double* __restrict__ wn, int64_t ut, const int* __restrict__ live,
@@ -818,11 +842,10 @@ normalize_step_kernel(const WB* __restrict__ w, VB* __restrict__ V, const RhsVec
       if (!si.active || (si.jdone >= 0 && si.jdone <= j)) continue;
     }
     const RhsVec r = rv[b];
-    const int64_t nb = (r.N + 63) / 64;
     if (blk * RW * blockDim.x >= r.N) continue;  // uniform over the block
     __syncthreads();  // the previous item's reads of nv_s and v_s are done
     if (threadIdx.x < 64) {
-      const double sum = wave_sum_partials(npart + (size_t)b * maxB, n_npart > 0 ? n_npart : (int)nb);
+      const double sum = wave_sum_partials(npart + (size_t)b * maxB, part_el > 0 ? (int)((r.N + part_el - 1) / part_el) : 1);
       if (threadIdx.x == 0) nv_s = sqrt(fmax(sum, 0.0));
     }
     __syncthreads();
@@ -1360,19 +1383,25 @@ struct Work {
 
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
-// 64-element runs per update block: four for long vectors (more than 64
-// chunks of kDotChunk: a quarter of the workgroups, which matters once most
-// right-hand sides of a wide batch are idle and their workgroups only
-// return), else one (the single-RHS solve keeps enough workgroups, and
-// normalize_step_kernel sums their per-64 parts itself)
-int update_runs(int64_t maxN) { return (maxN + kDotChunk - 1) / kDotChunk > 64 ? 4 : 1; }
+// 64-element runs per update block: four, with every thread on its own
+// element (gs_update_el_kernel), or one, whose four waves share the basis
+// vectors of its 64 elements (gs_update_kernel; short vectors then fill four
+// times the workgroups).  The line was drawn from whole solves (ms, split /
+// element form; 1-bit arrays of N unknowns):
+//   complex64 basis, GMRES(20): N = 5,760 1.74 / 1.77 (1 RHS), 3.20 / 3.02
+//   (32 RHS); 10,240 2.33 / 2.32, 5.15 / 4.58; 40,960 7.04 / 6.89, 31.9 / 26.6
+//   (with FP64 refinement 37.3 / 28.0);
+//   complex128 basis, GMRES(60), no preconditioner: 1,440 20.6 / 22.2 (1 RHS),
+//   32.8 / 34.4 (16 RHS); 10,240 199 / 202; 23,040 even.
+// It depends on the longest vector of the batch and not on its width.
+int update_runs(int64_t maxN, bool vb32) { return maxN > (vb32 ? kElementMin32 : kElementMin64) ? 4 : 1; }
 // basis vectors a folded update takes: the element-parallel kernel (long
 // vectors) holds more
 int fold_max_vec(int64_t maxN, bool vb32) {
-  return update_runs(maxN) == 4 && vb32 ? kFoldMaxVecEl : kFoldMaxVec;
+  return update_runs(maxN, vb32) == 4 && vb32 ? kFoldMaxVecEl : kFoldMaxVec;
 }
-int64_t fold_blocks(int64_t maxN) {
-  const int nsub = update_runs(maxN);
+int64_t fold_blocks(int64_t maxN, bool vb32) {
+  const int nsub = update_runs(maxN, vb32);
   return std::max<int64_t>(1, (maxN + 64 * nsub - 1) / (64 * nsub));
 }
 
@@ -1412,7 +1441,7 @@ Work layout_work(char* base, const BatchDesc& bd, int n_a, int n_blocks, int m, 
   w.cs = (double*)take((size_t)B * m * 8);
   w.sn = (double2*)take((size_t)B * m * 16);
   w.dpart = (double2*)take((size_t)B * (m + 1) * std::max(maxP, 1) * 16);
-  w.dpart2 = (double2*)take((size_t)B * std::min(m + 1, fold_max_vec(maxN, vb32)) * fold_blocks(maxN) * 16);
+  w.dpart2 = (double2*)take((size_t)B * std::min(m + 1, fold_max_vec(maxN, vb32)) * fold_blocks(maxN, vb32) * 16);
   w.hbuf = (double2*)take((size_t)B * (m + 1) * 16);
   w.hsum = (double2*)take((size_t)B * (m + 1) * 16);
   w.nsum = (double*)take((size_t)B * 8);
@@ -1597,8 +1626,8 @@ struct GmresRun {
     const int maxB = (int)((maxN + 63) / 64 + 1);
     // long vectors (more than 64 chunk partials per coefficient): sum the
     // partials once in their own launch rather than in every update block
-    const bool long_vec = maxP > 64;
-    const int nsub = update_runs(maxN);
+    const bool long_vec = maxP > kPartialsInUpdate;
+    const int nsub = update_runs(maxN, sizeof(VB) == sizeof(float2));
     const int nvec = j + 1;
     // inner-product items of dv vectors: the basis count padded to a power of
     // two up to dot_vec (the exchanges of the lane sums scale with dv)
@@ -1624,7 +1653,7 @@ struct GmresRun {
     // CGS2, first pass: inner products with the basis, then the update
     dots(run_slot(j));
     if (long_vec)
-      hipLaunchKernelGGL(finish_partials_kernel, dim3(nvec, B), dim3(256), 0, s, (const double2*)W.dpart, maxP, nvec,
+      hipLaunchKernelGGL(finish_partials_kernel, dim3((nvec + 3) / 4, B), dim3(256), 0, s, (const double2*)W.dpart, maxP, nvec,
                          W.rv, W.hsum, live, W.idle, kDotChunk);
     const double2* h0 = long_vec ? (const double2*)W.hsum : (const double2*)W.dpart;
     const int h0P = long_vec ? 1 : maxP, h0n = long_vec ? 1 : 0;
@@ -1673,23 +1702,24 @@ struct GmresRun {
       // long vectors it also takes ||w||^2, and the second pass runs only
       // where the first lost more than half of the squared norm (the first
       // pass's norm parts then stand for the RHS that skip it)
-      const int maxP2 = (int)fold_blocks(maxN);
+      const int maxP2 = (int)fold_blocks(maxN, sizeof(VB) == sizeof(float2));
       const bool sel = long_vec && nsub == 4 && selective_cgs2();
       update(nvec <= 8 ? 2 : 4, h0, h0P, h0n, sel ? 1 : 0, 0, kDotChunk, W.dpart2, maxP2, nullptr);
       if (sel)
         hipLaunchKernelGGL(finish_norm_kernel, dim3(B), dim3(256), 0, s, (const double*)W.npart, maxB, W.rv, W.nsum,
                            live, W.idle, nsub);
-      if (long_vec)
-        hipLaunchKernelGGL(finish_partials_kernel, dim3(nvec, B), dim3(256), 0, s, (const double2*)W.dpart2, maxP2,
-                           nvec, W.rv, W.hsum, live, W.idle, 64 * nsub);
-      update(0, long_vec ? (const double2*)W.hsum : (const double2*)W.dpart2, long_vec ? 1 : maxP2, long_vec ? 1 : 0,
-             1, 1, 64 * nsub, (double2*)nullptr, 0, sel ? (const double*)W.nsum : nullptr);
+      const bool fin2 = long_vec || maxP2 > kPartials2InUpdate;
+      if (fin2)
+        hipLaunchKernelGGL(finish_partials_kernel, dim3((nvec + 3) / 4, B), dim3(256), 0, s, (const double2*)W.dpart2,
+                           maxP2, nvec, W.rv, W.hsum, live, W.idle, 64 * nsub);
+      update(0, fin2 ? (const double2*)W.hsum : (const double2*)W.dpart2, fin2 ? 1 : maxP2, fin2 ? 1 : 0, 1, 1,
+             64 * nsub, (double2*)nullptr, 0, sel ? (const double*)W.nsum : nullptr);
     } else {
       update(0, h0, h0P, h0n, 0, 0, kDotChunk, (double2*)nullptr, 0, nullptr);
       // CGS2, second pass
       dots((int*)nullptr);
       if (long_vec)
-        hipLaunchKernelGGL(finish_partials_kernel, dim3(nvec, B), dim3(256), 0, s, (const double2*)W.dpart, maxP,
+        hipLaunchKernelGGL(finish_partials_kernel, dim3((nvec + 3) / 4, B), dim3(256), 0, s, (const double2*)W.dpart, maxP,
                            nvec, W.rv, W.hsum, live, W.idle, kDotChunk);
       update(0, h0, h0P, h0n, 1, 1, kDotChunk, (double2*)nullptr, 0, nullptr);
     }
@@ -1697,7 +1727,7 @@ struct GmresRun {
       hipLaunchKernelGGL(finish_norm_kernel, dim3(B), dim3(256), 0, s, (const double*)W.npart, maxB, W.rv, W.nsum,
                          live, W.idle, nsub);
     const double* np = long_vec ? W.nsum : W.npart;
-    const int npB = long_vec ? 1 : maxB, npN = long_vec ? 1 : 0;
+    const int npB = long_vec ? 1 : maxB, npE = long_vec ? 0 : 64 * nsub;
     // blocks of whole units (the preconditioner multiplies per unit)
     const int nthr = pre ? (256 / n_a) * n_a : 256;
     const int64_t nb_n = ceil_div((size_t)maxN, nthr);
@@ -1709,7 +1739,7 @@ struct GmresRun {
     const bool c64 = Z->near_dtype == R3M_C64;
 #define R3M_NORMALIZE(OT, MODE, XS)                                                                                  \
   hipLaunchKernelGGL((normalize_step_kernel<OT, MODE, VB, WB>), ngrid, dim3(nthr), glds, s, wv, V, W.rv, W.st, np, npB, \
-                     npN, W.H, W.g, W.cs, W.sn, m, j, tol, run_slot(j), W.wn, ut, live, W.Minv, batch->states, W.soff, \
+                     npE, W.H, W.g, W.cs, W.sn, m, j, tol, run_slot(j), W.wn, ut, live, W.Minv, batch->states, W.soff, \
                      n_a, n_states, XS, pu, W.idle, rl, B, nb_n, stage)
     if (ilu_r) {
       // V_{j+1}, then the next step's input M^-1 V_{j+1} by the colour solves
@@ -1722,7 +1752,7 @@ struct GmresRun {
       // RW rows per thread: blocks of RW times the units
       auto rows = [&](auto kern, int rw) {
         const int64_t nbr = ceil_div((size_t)maxN, (size_t)rw * nthr);
-        hipLaunchKernelGGL(kern, dim3(stride_grid(nbr * B)), dim3(nthr), glds, s, wv, V, W.rv, W.st, np, npB, npN,
+        hipLaunchKernelGGL(kern, dim3(stride_grid(nbr * B)), dim3(nthr), glds, s, wv, V, W.rv, W.st, np, npB, npE,
                            W.H, W.g, W.cs, W.sn, m, j, tol, run_slot(j), W.wn, ut, live, W.Minv, batch->states,
                            W.soff, n_a, n_states, (float*)W.xs, pu, W.idle, rl, B, nbr, stage);
       };
