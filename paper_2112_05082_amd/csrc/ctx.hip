@@ -422,6 +422,7 @@ int r3m_ctx_destroy(r3m_ctx ctx) {
   if (ctx->run_host) (void)hipHostFree(ctx->run_host);
   ctx->flag.release();
   ctx->geom.release();
+  ctx->post.release();
   ctx->fill_tab.release();
   ctx->fill_ws.release();
   for (auto& kv : ctx->batches) {

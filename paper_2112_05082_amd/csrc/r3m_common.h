@@ -123,6 +123,7 @@ struct r3m_ctx_s {
   std::mutex mu;
   r3m::DevBuf flag;  // int32 flags for device-side checks
   r3m::DevBuf geom;  // geometry tables
+  r3m::DevBuf post;  // scratch of the excitation and RCS calls (at most 128 MiB)
   r3m::DevBuf fill_tab, fill_ws;  // tiles of the fill, pair integrals of its near blocks (at most 64 MiB)
   std::map<r3m::BatchKey, r3m::BatchDesc*> batches;
   hipStream_t work_stream = nullptr;  // default-priority stream for graph replays
