@@ -64,6 +64,14 @@ __host__ __device__ constexpr int bitrev(int i) {
   return r;
 }
 
+// v (c + j sn) with the fused operations written out: left to the compiler,
+// which product of each difference is fused depends on the code around it, and
+// the transform forms (which must give the same bits) would differ
+template <typename T>
+__device__ __forceinline__ C2<T> rotate(C2<T> v, T c, T sn) {
+  return {fma(v.re, c, -(v.im * sn)), fma(v.re, sn, v.im * c)};
+}
+
 // in-register DFT of R <= 16 points, b_q = sum_r a_r exp(sgn 2 pi i r q / R)
 // (iterative radix-2 decimation in time on the bit-reversed input)
 template <typename T, int R, int SGN>
@@ -86,8 +94,7 @@ __device__ __forceinline__ void dft_regs(C2<T>* a) {
         } else if (m == 4) {
           t = {-SGN * v.im, SGN * v.re};
         } else {
-          const T c = (T)kCos16[m], sn = (T)(SGN * kSin16[m]);
-          t = {v.re * c - v.im * sn, v.re * sn + v.im * c};
+          t = rotate(v, (T)kCos16[m], (T)(SGN * kSin16[m]));
         }
         b[i + j] = {u.re + t.re, u.im + t.im};
         b[i + j + len / 2] = {u.re - t.re, u.im - t.im};
@@ -103,57 +110,104 @@ __device__ __forceinline__ void dft_regs(C2<T>* a) {
 // after every 16 elements (spreads the strided writes of the first stage)
 __device__ __forceinline__ int lds_at(int li, int e, int S) { return li * S + e + (e >> 4); }
 
-// One Stockham stage of radix R on the lines staged in LDS: with Ns the
-// product of the earlier radices, item j < G / R of a line takes the inputs
-// j + r G / R, multiplies input r by exp(sgn 2 pi i r k / (Ns R)) with
-// k = j mod Ns, applies the R-point DFT and writes output q to
-// (j / Ns) Ns R + k + q Ns.  A thread holds KE / R items in registers; the
-// barrier between the reads and the writes lets the stage work in place.
-template <typename T, int R, int KE, int SGN>
-__device__ __forceinline__ void stockham_stage(C2<T>* buf, const C2<T>* tw, int lgG, int lgNs, int n_items, int S) {
+// One Stockham stage of radix R on a workgroup's lines: with Ns the product of
+// the earlier radices, item j < G / R of a line takes the inputs j + r G / R,
+// multiplies input r by exp(sgn 2 pi i r k / (Ns R)) with k = j mod Ns, applies
+// the R-point DFT and writes output q to (j / Ns) Ns R + k + q Ns.  A thread
+// holds KE / R items in registers.  Lines are exchanged between stages through
+// LDS (in place: a barrier separates the reads from the writes); the first
+// stage takes its inputs from load(a, li, e) and the last hands its outputs to
+// store(v, li, e) instead, so that a line crosses LDS once per stage boundary
+// only, and all of a thread's loads are in flight before the first DFT (staged
+// through LDS on both sides, a load at a time, the column passes of sixteen
+// right-hand sides on 256 x 256 complex64 grids, 1 GB each, took 324 and 334
+// us, 3.1 TB/s; now 219 and 206, 4.7 TB/s; the row passes 187 and 196, now 119
+// and 126).
+// LF: adjacent threads take adjacent lines (a line's items otherwise).
+template <typename T, int R, int KE, int SGN, bool LF, bool FIRST, bool LAST, typename LoadF, typename StoreF>
+__device__ __forceinline__ void stockham_stage(C2<T>* buf, const C2<T>* tw, int lgG, int lgNs, int lg_lpw, int S,
+                                               const LoadF& load, const StoreF& store) {
   constexpr int LR = R == 2 ? 1 : R == 4 ? 2 : R == 8 ? 3 : 4;
   constexpr int IT = KE / R;
   const int lgQ = lgG - LR;  // items per line = G / R
+  const int n_items = 1 << (lgQ + lg_lpw);
   const int Ns = 1 << lgNs;
+  int li[IT], j[IT];
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int item = threadIdx.x + it * 256;
+    li[it] = LF ? item & ((1 << lg_lpw) - 1) : item >> lgQ;
+    j[it] = LF ? item >> lg_lpw : item & ((1 << lgQ) - 1);
+  }
   C2<T> a[IT][R];
+  if constexpr (FIRST) {
+    load(a, li, j, lgQ, n_items);
+  } else {
+    const int tws = lgG - lgNs - LR;  // exp(sgn 2 pi i r k / (Ns R)) = tw[r k G / (Ns R)]
 #pragma unroll
-  for (int it = 0; it < IT; ++it) {
-    const int item = threadIdx.x + it * 256;
-    if (item < n_items) {
-      const int li = item >> lgQ, j = item & ((1 << lgQ) - 1);
-      const int k = j & (Ns - 1);
-      const int tws = lgG - lgNs - LR;  // exp(sgn 2 pi i r k / (Ns R)) = tw[r k G / (Ns R)]
+    for (int it = 0; it < IT; ++it) {
+      if (threadIdx.x + it * 256 < n_items) {
+        const int k = j[it] & (Ns - 1);
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        C2<T> v = buf[lds_at(li, j + (r << lgQ), S)];
-        if (r > 0) {
-          const C2<T> w = tw[(r * k) << tws];
-          v = {v.re * w.re - v.im * w.im, v.re * w.im + v.im * w.re};
+        for (int r = 0; r < R; ++r) {
+          C2<T> v = buf[lds_at(li[it], j[it] + (r << lgQ), S)];
+          if (r > 0) {
+            const C2<T> w = tw[(r * k) << tws];
+            v = rotate(v, w.re, w.im);
+          }
+          a[it][r] = v;
         }
-        a[it][r] = v;
       }
-      dft_regs<T, R, SGN>(a[it]);
     }
   }
-  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < IT; ++it) dft_regs<T, R, SGN>(a[it]);
+  if (!FIRST && !LAST) __syncthreads();
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
-    const int item = threadIdx.x + it * 256;
-    if (item < n_items) {
-      const int li = item >> lgQ, j = item & ((1 << lgQ) - 1);
-      const int k = j & (Ns - 1);
-      const int o = ((j >> lgNs) << (lgNs + LR)) + k;
+    if (threadIdx.x + it * 256 < n_items) {
+      const int k = j[it] & (Ns - 1);
+      const int o = ((j[it] >> lgNs) << (lgNs + LR)) + k;
 #pragma unroll
-      for (int q = 0; q < R; ++q) buf[lds_at(li, o + (q << lgNs), S)] = a[it][q];
+      for (int q = 0; q < R; ++q) {
+        if constexpr (LAST)
+          store(a[it][q], li[it], o + (q << lgNs));
+        else
+          buf[lds_at(li[it], o + (q << lgNs), S)] = a[it][q];
+      }
     }
   }
-  __syncthreads();
+  if (!LAST) __syncthreads();
 }
 
-// Mixed-radix Stockham transforms of grid lines staged in LDS (forward:
-// exp(-2 pi i j k / G); inverse: exp(+...), unnormalised), radix KE stages
-// (16 in single, 8 in double precision) and one smaller stage for the rest
-// of log2 G.  Grids are row-major Gy x Gx (element (gx, gy) at gy Gx + gx);
+// every stage of a pass: radix KE stages (16 in single, 8 in double precision)
+// and one smaller stage for the rest of log2 G
+template <typename T, int KE, int SGN, bool LOAD_LF, bool STORE_LF, typename LoadF, typename StoreF>
+__device__ __forceinline__ void stockham_lines(C2<T>* buf, const C2<T>* tw, int lgG, int lg_lpw, int S,
+                                               const LoadF& load, const StoreF& store) {
+  constexpr int LKE = KE == 16 ? 4 : 3;
+  if (lgG <= LKE) {  // one stage (thread map of the load side)
+    switch (lgG) {
+      case 1: return stockham_stage<T, 2, KE, SGN, LOAD_LF, true, true>(buf, tw, lgG, 0, lg_lpw, S, load, store);
+      case 2: return stockham_stage<T, 4, KE, SGN, LOAD_LF, true, true>(buf, tw, lgG, 0, lg_lpw, S, load, store);
+      case 3: return stockham_stage<T, 8, KE, SGN, LOAD_LF, true, true>(buf, tw, lgG, 0, lg_lpw, S, load, store);
+      default: return stockham_stage<T, KE, KE, SGN, LOAD_LF, true, true>(buf, tw, lgG, 0, lg_lpw, S, load, store);
+    }
+  }
+  stockham_stage<T, KE, KE, SGN, LOAD_LF, true, false>(buf, tw, lgG, 0, lg_lpw, S, load, store);
+  int lgNs = LKE;
+  for (; lgNs + LKE < lgG; lgNs += LKE)
+    stockham_stage<T, KE, KE, SGN, LOAD_LF, false, false>(buf, tw, lgG, lgNs, lg_lpw, S, load, store);
+  switch (lgG - lgNs) {
+    case 1: return stockham_stage<T, 2, KE, SGN, STORE_LF, false, true>(buf, tw, lgG, lgNs, lg_lpw, S, load, store);
+    case 2: return stockham_stage<T, 4, KE, SGN, STORE_LF, false, true>(buf, tw, lgG, lgNs, lg_lpw, S, load, store);
+    case 3: return stockham_stage<T, 8, KE, SGN, STORE_LF, false, true>(buf, tw, lgG, lgNs, lg_lpw, S, load, store);
+    default: return stockham_stage<T, KE, KE, SGN, STORE_LF, false, true>(buf, tw, lgG, lgNs, lg_lpw, S, load, store);
+  }
+}
+
+// Mixed-radix Stockham transforms of grid lines (forward: exp(-2 pi i j k / G);
+// inverse: exp(+...), unnormalised).  Grids are row-major Gy x Gx (element (gx, gy) at gy Gx + gx);
 // a pass transforms every row (elements adjacent) or every column (elements
 // Gx apart) of n_grids grids.  A workgroup takes lpw <= 256 KE / G adjacent
 // lines of one grid: along rows consecutive threads move consecutive
@@ -176,7 +230,13 @@ __device__ __forceinline__ void stockham_stage(C2<T>* buf, const C2<T>* tw, int 
 // With relaxed weights w[u][s] (a blended codebook) every channel c = s n_a + r
 // is active: kFwdRows reads w[u][s] x[u][r], and kInvRows writes
 // w[u][s] y~[u][c] / (Gx Gy) to a macro buffer whose sum over s is y[u][r].
-enum FftMode { kPlainRows, kPlainCols, kFwdRows, kFwdCols, kInvCols, kInvRows };
+// The spectra of a store are built by two more (grid g = m n + c, no
+// right-hand sides):
+//   kEmbedRows  rows of the circulant embedding, read from the displacement
+//               blocks (line-fastest: adjacent grids are adjacent entries of
+//               a block), only the 2 Dy + 1 rows that hold any;
+//   kEmbedCols  columns, the other rows taken as zero.
+enum FftMode { kFwdRows, kFwdCols, kInvCols, kInvRows, kEmbedRows, kEmbedCols };
 
 template <typename T>
 struct FftArgs {
@@ -199,6 +259,8 @@ struct FftArgs {
   // ymacro [unit][n] (summed over states afterwards)
   const double* wts;
   C2<T>* ymacro;
+  const double2* dense;  // kEmbedRows: blocks [slot][m][n] of half-extent (Dx, Dy)
+  int Dx, Dy;
   int macro_plain;  // kInvRows with wts: write y~ itself (the macro product Z P(w) x), no weights
   const int* live;
   const int* idle;  // per right-hand side (nullable): lines of b with idle[b] != 0 are left alone
@@ -212,16 +274,16 @@ constexpr int fft_ke() {
 template <typename T, int MODE, typename VT>
 __global__ void __launch_bounds__(256) fft_kernel(FftArgs<T> A) {
   if (A.live && *A.live == 0) return;
-  constexpr bool rows = MODE == kPlainRows || MODE == kFwdRows || MODE == kInvRows;
-  constexpr bool masked = MODE >= kFwdRows;
+  constexpr bool rows = MODE == kFwdRows || MODE == kInvRows || MODE == kEmbedRows;
+  constexpr bool masked = MODE <= kInvRows;
   // the compacting row passes take one row of lpw consecutive channels (grids)
   // of one right-hand side, so that the compact vector is read (kFwdRows) or
   // written (kInvRows) in runs of adjacent rows A(s) of a unit; the other
   // passes take lpw adjacent lines of one grid
-  constexpr bool chan = MODE == kFwdRows || MODE == kInvRows;
+  constexpr bool chan = MODE == kFwdRows || MODE == kInvRows || MODE == kEmbedRows;
   // thread -> (line, element) maps: line-fastest for columns and for the
   // compact side of the compacting passes, element-fastest otherwise
-  constexpr bool load_lf = !rows || MODE == kFwdRows;
+  constexpr bool load_lf = !rows || MODE == kFwdRows || MODE == kEmbedRows;
   constexpr bool store_lf = !rows || MODE == kInvRows;
   constexpr int SGN = MODE == kInvCols || MODE == kInvRows ? 1 : -1;
   constexpr int KE = fft_ke<T>();
@@ -246,13 +308,16 @@ __global__ void __launch_bounds__(256) fft_kernel(FftArgs<T> A) {
     lig0 = (int)(l0 & ((1 << A.lg_lpg) - 1));
   }
   int Lx = 0, Ly = 0, c0 = 0;
-  RhsDev R{};
+  RhsDev R_{};
+  const int Gy = 1 << (rows ? A.lg_lpg : lgG);
+  auto no_block = [&](int gy) { return gy > A.Dy && gy < Gy - A.Dy; };  // a row of the embedding without blocks
+  if (MODE == kEmbedRows && no_block(lig0)) return;
   if (masked) {
     const int b = (int)(g0 / A.n);
     c0 = (int)(g0 - (int64_t)b * A.n);
-    R = A.rhs[b];
-    Lx = R.Lx;
-    Ly = R.Ly;
+    R_ = A.rhs[b];
+    Lx = R_.Lx;
+    Ly = R_.Ly;
     if (chan && lig0 >= Ly) return;  // a row past the array
   }
   // a workgroup's lines belong to one right-hand side (grids are [B][n])
@@ -265,7 +330,7 @@ __global__ void __launch_bounds__(256) fft_kernel(FftArgs<T> A) {
       const int e = A.ext[c - A.n_st];
       return e == 0 || (e == 1 && gx > 0) || (e == 2 && gy > 0) ? A.n_a + c - A.n_st : -2;
     }
-    const int s = min((int)A.states[R.state_off + u], A.n_states - 1);
+    const int s = min((int)A.states[R_.state_off + u], A.n_states - 1);
     const int r = c - s * A.n_a;
     return r >= 0 && r < A.n_a ? r : -1;
   };
@@ -279,68 +344,86 @@ __global__ void __launch_bounds__(256) fft_kernel(FftArgs<T> A) {
     sincospi_t<T>((T)(2 * m) / (T)G, &sn, &cs);
     tw[m] = {cs, (T)SGN * sn};
   }
-  const int tot = lpw << lgG;
-  for (int t = threadIdx.x; t < tot; t += blockDim.x) {
-    const int li = load_lf ? t & (lpw - 1) : t >> lgG;
-    const int e = load_lf ? t >> A.lg_lpw : t & (G - 1);
+  auto at_line = [&](int li, int e, int& gx, int& gy) {
     const int line = chan ? lig0 : lig0 + li;
-    const int gx = rows ? e : line, gy = rows ? line : e;
-    C2<T> v = {0, 0};
-    if (MODE == kFwdRows) {
-      if (gx < Lx) {
-        const int64_t u = (int64_t)gy * Lx + gx;
-        if (A.wts) {
-          const int c = c0 + li, s = c / A.n_a, r = c - s * A.n_a;
-          const double wv = A.wts[(R.unit_off + u) * A.n_states + s];
-          const VT* xv = (const VT*)A.x + ((R.unit_off + u) * A.n_a + r) * 2;
-          v = {(T)(wv * (double)xv[0]), (T)(wv * (double)xv[1])};
-        } else {
-          const int r = active(u, gx, gy, c0 + li);
-          if (r >= 0) {
-            const VT* xv = (const VT*)A.x + ((R.unit_off + u) * A.n_red + r) * 2;
-            v = {(T)xv[0], (T)xv[1]};
+    gx = rows ? e : line;
+    gy = rows ? line : e;
+  };
+  // inputs of a thread's items: element j + (r << lgQ) of line li
+  auto load = [&](auto& a, const auto& li, const auto& j, int lgQ, int n_items) {
+    constexpr int IT = sizeof(a) / sizeof(a[0]), R = sizeof(a[0]) / sizeof(a[0][0]);
+    if constexpr (MODE == kFwdRows) {
+      // the states first, then the entries they select
+      int rr[IT][R];
+#pragma unroll
+      for (int it = 0; it < IT; ++it)
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const int gx = j[it] + (r << lgQ);
+          rr[it][r] = -1;
+          if ((int)threadIdx.x + it * 256 < n_items && gx < Lx)
+            rr[it][r] = A.wts ? 0 : active((int64_t)lig0 * Lx + gx, gx, lig0, c0 + li[it]);
+        }
+#pragma unroll
+      for (int it = 0; it < IT; ++it)
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          a[it][r] = {0, 0};
+          if (rr[it][r] >= 0) {
+            const int64_t u = (int64_t)lig0 * Lx + j[it] + (r << lgQ);
+            if (A.wts) {
+              const int c = c0 + li[it], s = c / A.n_a, ra = c - s * A.n_a;
+              const double wv = A.wts[(R_.unit_off + u) * A.n_states + s];
+              const VT* xv = (const VT*)A.x + ((R_.unit_off + u) * A.n_a + ra) * 2;
+              a[it][r] = {(T)(wv * (double)xv[0]), (T)(wv * (double)xv[1])};
+            } else {
+              const VT* xv = (const VT*)A.x + ((R_.unit_off + u) * A.n_red + rr[it][r]) * 2;
+              a[it][r] = {(T)xv[0], (T)xv[1]};
+            }
           }
         }
-      }
-    } else if (MODE == kFwdCols) {
-      if (gy < Ly) v = *grid_at(li, gx, gy);
     } else {
-      v = *grid_at(li, gx, gy);
+#pragma unroll
+      for (int it = 0; it < IT; ++it)
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          int gx, gy;
+          at_line(li[it], j[it] + (r << lgQ), gx, gy);
+          bool in = (int)threadIdx.x + it * 256 < n_items;
+          a[it][r] = {0, 0};
+          if constexpr (MODE == kEmbedRows) {
+            const int dx = gx <= A.Dx ? gx : gx - G, dy = gy <= A.Dy ? gy : gy - Gy;
+            if (in && dx >= -A.Dx) {
+              const double2 z = A.dense[((int64_t)(dy + A.Dy) * (2 * A.Dx + 1) + (dx + A.Dx)) * A.n + g0 + li[it]];
+              a[it][r] = {(T)z.x, (T)z.y};
+            }
+          } else {
+            if (MODE == kFwdCols) in = in && gy < Ly;
+            if (MODE == kEmbedCols) in = in && !no_block(gy);
+            if (in) a[it][r] = *grid_at(li[it], gx, gy);
+          }
+        }
     }
-    buf[lds_at(li, e, S)] = v;
-  }
-  __syncthreads();
-  constexpr int LKE = KE == 16 ? 4 : 3;
-  int lgNs = 0;
-  for (; lgNs + LKE <= lgG; lgNs += LKE) stockham_stage<T, KE, KE, SGN>(buf, tw, lgG, lgNs, tot >> LKE, S);
-  switch (lgG - lgNs) {
-    case 1: stockham_stage<T, 2, KE, SGN>(buf, tw, lgG, lgNs, tot >> 1, S); break;
-    case 2: stockham_stage<T, 4, KE, SGN>(buf, tw, lgG, lgNs, tot >> 2, S); break;
-    case 3: stockham_stage<T, 8, KE, SGN>(buf, tw, lgG, lgNs, tot >> 3, S); break;
-    default: break;
-  }
+  };
   const T scale = T(1) / (T)((int64_t)1 << lgG2);
-  for (int t = threadIdx.x; t < tot; t += blockDim.x) {
-    const int li = store_lf ? t & (lpw - 1) : t >> lgG;
-    const int e = store_lf ? t >> A.lg_lpw : t & (G - 1);
-    const int line = chan ? lig0 : lig0 + li;
-    const int gx = rows ? e : line, gy = rows ? line : e;
-    const C2<T> v = buf[lds_at(li, e, S)];
+  auto store = [&](const C2<T>& v, int li, int e) {
+    int gx, gy;
+    at_line(li, e, gx, gy);
     if (MODE == kInvRows) {
       if (gx < Lx) {
         const int64_t u = (int64_t)gy * Lx + gx;
         if (A.wts) {
           const int c = c0 + li, s = c / A.n_a;
-          const T ws = (A.macro_plain ? T(1) : (T)A.wts[(R.unit_off + u) * A.n_states + s]) * scale;
-          A.ymacro[(R.unit_off + u) * A.n + c] = {v.re * ws, v.im * ws};
+          const T ws = (A.macro_plain ? T(1) : (T)A.wts[(R_.unit_off + u) * A.n_states + s]) * scale;
+          A.ymacro[(R_.unit_off + u) * A.n + c] = {v.re * ws, v.im * ws};
         } else {
           const int r = active(u, gx, gy, c0 + li);
           if (r >= 0) {
-            VT* yv = (VT*)A.y + ((R.unit_off + u) * A.n_red + r) * 2;
+            VT* yv = (VT*)A.y + ((R_.unit_off + u) * A.n_red + r) * 2;
             yv[0] = (VT)(v.re * scale);
             yv[1] = (VT)(v.im * scale);
           } else if (r == -2) {
-            VT* yv = (VT*)A.y + ((R.unit_off + u) * A.n_red + A.n_a + c0 + li - A.n_st) * 2;
+            VT* yv = (VT*)A.y + ((R_.unit_off + u) * A.n_red + A.n_a + c0 + li - A.n_st) * 2;
             yv[0] = yv[1] = (VT)0;
           }
         }
@@ -350,7 +433,8 @@ __global__ void __launch_bounds__(256) fft_kernel(FftArgs<T> A) {
     } else {
       *grid_at(li, gx, gy) = v;
     }
-  }
+  };
+  stockham_lines<T, KE, SGN, load_lf, store_lf>(buf, tw, lgG, A.lg_lpw, S, load, store);
 }
 
 int ilog2(int v) {
@@ -372,8 +456,8 @@ int fft_lpw_log(int lgG, int lg_lpg) {
 // largest power of two dividing n that fits)
 template <typename T, int MODE, typename VT>
 void fft_pass(FftArgs<T> A, int lgGx, int lgGy, int64_t n_grids, hipStream_t s) {
-  constexpr bool rows = MODE == kPlainRows || MODE == kFwdRows || MODE == kInvRows;
-  constexpr bool chan = MODE == kFwdRows || MODE == kInvRows;
+  constexpr bool rows = MODE == kFwdRows || MODE == kInvRows || MODE == kEmbedRows;
+  constexpr bool chan = rows;
   A.lgG = rows ? lgGx : lgGy;
   A.lg_lpg = rows ? lgGy : lgGx;
   int64_t n_wg;
@@ -474,9 +558,10 @@ __device__ __forceinline__ void stage2d(float2* __restrict__ buf, int Sx, const 
         if (e < nz) v = GSRC ? gm[((int64_t)gy << lg_lines) + gx] : buf[at2(gx, gy, Sx)];
         if (r > 0 && lgNs > 0) {
           const float2 w = tw[(r * k) << tws];
-          v = make_float2(v.x * w.x - v.y * w.y, v.x * w.y + v.y * w.x);
+          a[it][r] = rotate(C2<float>{v.x, v.y}, w.x, w.y);
+        } else {
+          a[it][r] = {v.x, v.y};
         }
-        a[it][r] = {v.x, v.y};
       }
       dft_regs<float, R, SGN>(a[it]);
     }
@@ -745,29 +830,27 @@ void fft2_pass(const Fft2Args& A, hipStream_t s) {
   }
 }
 
-// Circulant embedding of the displacement blocks dense[slot][m][n]
-// (complex128, slot = (dy + Dy)(2 Dx + 1) + dx + Dx) into grids
-// [m][n][Gy][Gx]: entry (gx, gy) holds Z(d)[m][n] for gx = dx mod Gx,
-// gy = dy mod Gy, and zero where no |dx| <= Dx, |dy| <= Dy maps.
+// Spectra of a store: the circulant embedding of the displacement blocks
+// dense[slot][m][n] (complex128, slot = (dy + Dy)(2 Dx + 1) + dx + Dx; entry
+// (gx, gy) holds Z(d)[m][n] for gx = dx mod Gx, gy = dy mod Gy, zero where no
+// |dx| <= Dx, |dy| <= Dy maps) goes straight into the row transforms.  A
+// separate embedding pass read one 16-byte entry per line: 1-bit blocks for
+// 64x64 arrays (1.65 GB in, 0.84 GB out, 0.52 ms at the copy rate) took 0.75 ms
+// there plus 0.92 for the transforms; the two passes now take 0.54 + 0.31 ms.
+// One pass with whole grids in LDS was no faster (four 64x64 grids to a
+// workgroup 0.82 ms against 0.87, 128x128 ones 1.15 against 0.85): a grid takes
+// 16 bytes of every block, and a workgroup's grids together a 64-byte run.
 template <typename T>
-__global__ void __launch_bounds__(256)
-spec_embed_kernel(const double2* __restrict__ dense, int n, int Dx, int Dy, int Gx, int Gy, C2<T>* __restrict__ out) {
-  const int64_t G2 = (int64_t)Gx * Gy;
-  const int64_t total = (int64_t)n * n * G2;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t mn = e / G2;
-    const int64_t k = e - mn * G2;
-    const int gy = (int)(k / Gx), gx = (int)(k - (int64_t)gy * Gx);
-    const int dx = gx <= Dx ? gx : gx - Gx;
-    const int dy = gy <= Dy ? gy : gy - Gy;
-    C2<T> v = {0, 0};
-    if (dx >= -Dx && dy >= -Dy) {
-      const int64_t slot = (int64_t)(dy + Dy) * (2 * Dx + 1) + (dx + Dx);
-      const double2 z = dense[slot * n * n + mn];
-      v = {(T)z.x, (T)z.y};
-    }
-    out[e] = v;
-  }
+void spec_build(const double2* dense, int n, int Dx, int Dy, C2<T>* out, hipStream_t s) {
+  const int lgGx = ilog2(next_pow2(2 * Dx + 1)), lgGy = ilog2(next_pow2(2 * Dy + 1));
+  FftArgs<T> A{};
+  A.data = out;
+  A.n = n * n;
+  A.dense = dense;
+  A.Dx = Dx;
+  A.Dy = Dy;
+  fft_pass<T, kEmbedRows, T>(A, lgGx, lgGy, (int64_t)n * n, s);
+  fft_pass<T, kEmbedCols, T>(A, lgGx, lgGy, (int64_t)n * n, s);
 }
 
 // Y^[b][m][k] = sum_c Z^[m][c][k] X^[b][c][k]: one n x n product per
@@ -1568,23 +1651,10 @@ int r3m_build_spectral(r3m_ctx ctx, const void* dense_dev, int32_t n, int32_t Dx
     R3M_REQUIRE(spec_bytes >= spectra_bytes(n, Dx, Dy, dtype), R3M_ERR_BUFFER_TOO_SMALL,
                 "spectra buffer too small");
     R3M_CHECK_HIP(hipSetDevice(ctx->device));
-    const int64_t total = (int64_t)n * n * Gx * Gy;
-    const unsigned blocks = (unsigned)std::min<int64_t>((total + 255) / 256, 1 << 20);
-    if (dtype == R3M_SPEC_C128) {
-      hipLaunchKernelGGL(spec_embed_kernel<double>, dim3(blocks), dim3(256), 0, stream, (const double2*)dense_dev, n,
-                         Dx, Dy, Gx, Gy, (C2<double>*)spec_dev);
-      FftArgs<double> A{};
-      A.data = (C2<double>*)spec_dev;
-      fft_pass<double, kPlainRows, double>(A, ilog2(Gx), ilog2(Gy), (int64_t)n * n, stream);
-      fft_pass<double, kPlainCols, double>(A, ilog2(Gx), ilog2(Gy), (int64_t)n * n, stream);
-    } else {
-      hipLaunchKernelGGL(spec_embed_kernel<float>, dim3(blocks), dim3(256), 0, stream, (const double2*)dense_dev, n,
-                         Dx, Dy, Gx, Gy, (C2<float>*)spec_dev);
-      FftArgs<float> A{};
-      A.data = (C2<float>*)spec_dev;
-      fft_pass<float, kPlainRows, float>(A, ilog2(Gx), ilog2(Gy), (int64_t)n * n, stream);
-      fft_pass<float, kPlainCols, float>(A, ilog2(Gx), ilog2(Gy), (int64_t)n * n, stream);
-    }
+    if (dtype == R3M_SPEC_C128)
+      spec_build(static_cast<const double2*>(dense_dev), n, Dx, Dy, static_cast<C2<double>*>(spec_dev), stream);
+    else
+      spec_build(static_cast<const double2*>(dense_dev), n, Dx, Dy, static_cast<C2<float>*>(spec_dev), stream);
     R3M_CHECK_HIP(hipGetLastError());
   });
 }
