@@ -903,6 +903,77 @@ __global__ void __launch_bounds__(256) near_mfma_kernel(NearArgs<S> A, const int
   near_body<S, NA>(A, blockIdx.x);
 }
 
+// All-dense stores, few unit pairs: y_i = sum_j Z(i - j)[A(s_i), A(s_j)] x_j in
+// one launch, without lists, partial slots or their reduction.  A workgroup
+// owns eight rows of one observer unit; its kDirectWaves waves take the source
+// units in turn (wave w: j = w, w + kDirectWaves, ...) and are added in wave
+// order.  Lane = (row, one of eight column lanes), so a row's entries are read
+// as 128-byte runs (complex128); the sums stay in registers over all sources
+// and the column lanes are summed once at the end.  Bound by the blocks'
+// passage from L2 (n_a^2 entries per pair: 10x10 x 16 units, 160k pairs, 453
+// us, 9 TB/s in complex128, where the slab kernel took 1,144) and by launch
+// latency (6x6: 13 us per call, 37 with the lists' seven launches).
+// bad (nullable): kDeferredBadState is set in it for a state >= n_states.
+constexpr int kDirectWaves = 8;
+template <typename S, typename XI, typename YO, int NA>
+__global__ void __launch_bounds__(64 * kDirectWaves)
+dense_direct_kernel(const RhsDev* __restrict__ rhs, const uint8_t* __restrict__ states, const S* __restrict__ near,
+                    int Nx, int Ny, int n, int n_states, const XI* __restrict__ x, YO* __restrict__ y,
+                    const int* __restrict__ live, const int* __restrict__ idle, int* __restrict__ bad) {
+  if (live && *live == 0) return;  // every right-hand side has converged
+  if (idle && idle[blockIdx.y]) return;
+  constexpr int RG = NA / 8, CK = NA / 8;
+  __shared__ S part[kDirectWaves][8][2];
+  const RhsDev R = rhs[blockIdx.y];
+  const int u = blockIdx.x / RG, rg = blockIdx.x % RG;
+  const int units = R.Lx * R.Ly;
+  if (u >= units) return;
+  const uint8_t* st = states + R.state_off;
+  const int raw = st[u];
+  if (bad && rg == 0 && threadIdx.x == 0 && raw >= n_states) atomicOr(bad, kDeferredBadState);
+  const int si = min(raw, n_states - 1);
+  const int ix = u % R.Lx, iy = u / R.Lx;
+  const int lane = threadIdx.x & 63, cl = lane & 7;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const Cx<S>* zr = reinterpret_cast<const Cx<S>*>(near) + (size_t)(si * NA + rg * 8 + (lane >> 3)) * n + cl;
+  const Cx<XI>* xr = reinterpret_cast<const Cx<XI>*>(x) + (size_t)R.unit_off * NA + cl;
+  S re = 0, im = 0;
+#pragma unroll 2
+  for (int j = wave; j < units; j += kDirectWaves) {
+    const int jy = j / R.Lx, jx = j - jy * R.Lx;
+    const int slot = (iy - jy + Ny) * (2 * Nx + 1) + (ix - jx + Nx);
+    const int sj = min((int)st[j], n_states - 1);
+    const Cx<S>* zp = zr + (size_t)slot * n * n + sj * NA;
+    const Cx<XI>* xp = xr + (size_t)j * NA;
+    Cx<S> zv[CK];
+    Cx<XI> xv[CK];
+#pragma unroll
+    for (int k = 0; k < CK; ++k) {
+      zv[k] = zp[8 * k];
+      xv[k] = xp[8 * k];
+    }
+#pragma unroll
+    for (int k = 0; k < CK; ++k) cmac(re, im, zv[k], Cx<S>{(S)xv[k].re, (S)xv[k].im});
+  }
+#pragma unroll
+  for (int o = 4; o >= 1; o >>= 1) {
+    re += __shfl_xor(re, o);
+    im += __shfl_xor(im, o);
+  }
+  if (cl == 0) {
+    part[wave][lane >> 3][0] = re;
+    part[wave][lane >> 3][1] = im;
+  }
+  __syncthreads();
+  if (threadIdx.x < 16) {
+    const int r = threadIdx.x >> 1, c = threadIdx.x & 1;
+    S t = part[0][r][c];
+#pragma unroll
+    for (int w = 1; w < kDirectWaves; ++w) t += part[w][r][c];
+    y[2 * ((size_t)(R.unit_off + u) * NA + rg * 8 + r) + c] = (YO)t;
+  }
+}
+
 // Far and near field in one launch: the first near_wgs workgroups take the
 // near items (matrix cores), the rest the far tiles (vector units), so the
 // two kinds of work share the chip.  near_wgs is a multiple of 8, which keeps
@@ -1471,6 +1542,29 @@ static bool near_on_mfma(const r3m_store* Z) {
   return near_count(Z) <= 128 && ((size_t)2 * n_a + kNearCols) * (2 * n_a + 1) * es <= 96 * 1024;
 }
 
+// All-dense stores on the one-launch direct product: few unit pairs, or small
+// arrays where the slab kernel would take over from the matrix-core lists.
+// The lines from whole products (us, lists or slab / direct; complex128,
+// complex64): against the lists (up to 6x6 units) 6x6 alone 36.5 / 13.2, 30.4
+// / 13.3; 4x4 x 128 (33k pairs) 80 / 54, 55 / 51; 6x6 x 32 (41k) 95 / 88, 51 /
+// 62.  Against the slab kernel 10x10 106 / 33, 49 / 20; 12x12 x 24 (498k) 2,605
+// / 1,450, 1,182 / 731; 14x14 x 4 (154k) 528 / 461, 226 / 237; 20x20 (160k) 454
+// / 475, 214 / 238.
+constexpr int64_t kDirectPairsLists = (int64_t)1 << 15, kDirectPairsSlab = (int64_t)1 << 17;
+constexpr int64_t kDirectUnits = 144;
+static bool dense_direct(const r3m_store* Z, const BatchDesc& bd) {
+  if (store_is_spectral(Z) || store_has_far(Z)) return false;
+  const bool lists = near_on_mfma(Z);
+  if (!lists && bd.max_units <= kDirectUnits) return true;
+  const int64_t most = lists ? kDirectPairsLists : kDirectPairsSlab;
+  int64_t pairs = 0;
+  for (int64_t u : bd.n_units) {
+    pairs += u * u;
+    if (pairs > most) return false;
+  }
+  return true;
+}
+
 // near partial slots: one per displacement on the matrix-core path; otherwise
 // one displacement per workgroup for small batches, fewer groups (longer
 // loops) when the batch already fills the chip
@@ -1528,7 +1622,7 @@ size_t near_lists_bytes_bound(int n_states, const BatchDesc& bd) {
 // builds the near retrieval lists of (batch, codebook states) at lists_dev
 void build_near_lists(const r3m_store* Z, const BatchDesc& bd, const uint8_t* states, void* lists_dev,
                       hipStream_t stream) {
-  if (!near_on_mfma(Z)) return;
+  if (!near_on_mfma(Z) || dense_direct(Z, bd)) return;
   NearLists L = near_lists((char*)lists_dev, Z, bd);
   const int Nx = std::min(Z->near_radius, Z->Dx), Ny = std::min(Z->near_radius, Z->Dy);
   hipLaunchKernelGGL(zero_ints_kernel, dim3(ceil_div((size_t)L.n_cls, 256)), dim3(256), 0, stream, L.counts,
@@ -1645,10 +1739,24 @@ static void launch_far_mfma(const r3m_store* Z, const BatchDesc& bd, const uint8
   }
 }
 
+template <typename S, typename XI, typename YO>
+static void launch_direct(const r3m_store* Z, const BatchDesc& bd, const uint8_t* states, const XI* x, YO* y,
+                          hipStream_t stream, const int* live, const int* idle, int* bad) {
+  const int n_a = Z->n / Z->n_states;
+  auto kern = n_a == 40 ? dense_direct_kernel<S, XI, YO, 40> : dense_direct_kernel<S, XI, YO, 64>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(bd.max_units * (n_a / 8)), bd.B), dim3(64 * kDirectWaves), 0, stream,
+                     bd.rhs, states, (const S*)Z->near, Z->Dx, Z->Dy, Z->n, Z->n_states, x, y, live, idle, bad);
+  R3M_CHECK_HIP(hipGetLastError());
+}
+
 template <typename S, typename XT>
 static void launch_core(const r3m_store* Z, const BatchDesc& bd, const uint8_t* states, const S* xs, XT* y,
                         char* part, const void* lists, int chunks, hipStream_t stream,
                         const int* live = nullptr, const int* idle = nullptr) {
+  if (dense_direct(Z, bd)) {
+    launch_direct<S, S, XT>(Z, bd, states, xs, y, stream, live, idle, nullptr);
+    return;
+  }
   const int n_a = Z->n / Z->n_states;
   const int Nx = std::min(Z->near_radius, Z->Dx), Ny = std::min(Z->near_radius, Z->Dy);
   const bool far = store_has_far(Z);
@@ -1744,7 +1852,23 @@ static void launch_core(const r3m_store* Z, const BatchDesc& bd, const uint8_t* 
 
 template <typename S, typename XT>
 static void launch_typed(const r3m_store* Z, const BatchDesc& bd, const uint8_t* states, const void* x, void* y,
-                         void* partial, const void* lists, int chunks, hipStream_t stream, const int* idle) {
+                         void* partial, const void* lists, int chunks, hipStream_t stream, const int* idle,
+                         int* bad) {
+  if (dense_direct(Z, bd)) {
+    // the product reads x while it writes y: where the two overlap it writes
+    // the workspace, which is copied to y
+    const int n_a = Z->n / Z->n_states;
+    const size_t vec = (size_t)bd.total_units * n_a * 2 * sizeof(XT);
+    const bool apart = (const char*)x + vec <= (const char*)y || (const char*)y + vec <= (const char*)x;
+    XT* out = apart ? (XT*)y : (XT*)partial;
+    launch_direct<S, XT, XT>(Z, bd, states, (const XT*)x, out, stream, nullptr, idle, bad);
+    if (!apart) {
+      hipLaunchKernelGGL((convert_flat_kernel<XT, XT>), dim3(ceil_div((size_t)bd.max_units * n_a, 256), bd.B),
+                         dim3(256), 0, stream, bd.rhs, n_a, (const XT*)out, (XT*)y);
+      R3M_CHECK_HIP(hipGetLastError());
+    }
+    return;
+  }
   const int n_a = Z->n / Z->n_states;
   const bool far = store_has_far(Z);
   const int hg = near_groups(Z, bd);
@@ -1941,7 +2065,7 @@ bool plan_valid(const r3m_store* Z, const BatchDesc& bd, int plan) {
 // current near lists (build_near_lists), or NULL for the ones inside partial
 void launch_matvec(r3m_ctx ctx, const r3m_store* Z, const BatchDesc& bd, const uint8_t* states,
                    r3m_dtype vec_dtype, const void* x, void* y, void* partial, const void* lists, int chunks,
-                   hipStream_t stream, const int* idle) {
+                   hipStream_t stream, const int* idle, int* bad) {
   (void)ctx;
   if (store_is_spectral(Z)) {
     launch_spectral(Z, bd, states, vec_dtype, x, vec_dtype, y, partial, stream, nullptr, idle, chunks);
@@ -1950,11 +2074,11 @@ void launch_matvec(r3m_ctx ctx, const r3m_store* Z, const BatchDesc& bd, const u
   if (!lists) lists = workspace_lists(partial, bd, Z);
   if (Z->near_dtype == R3M_C128) {
     R3M_REQUIRE(vec_dtype == R3M_C128, R3M_ERR_UNSUPPORTED, "a C128 store needs C128 vectors");
-    launch_typed<double, double>(Z, bd, states, x, y, partial, lists, chunks, stream, idle);
+    launch_typed<double, double>(Z, bd, states, x, y, partial, lists, chunks, stream, idle, bad);
   } else if (vec_dtype == R3M_C64) {
-    launch_typed<float, float>(Z, bd, states, x, y, partial, lists, chunks, stream, idle);
+    launch_typed<float, float>(Z, bd, states, x, y, partial, lists, chunks, stream, idle, bad);
   } else {
-    launch_typed<float, double>(Z, bd, states, x, y, partial, lists, chunks, stream, idle);
+    launch_typed<float, double>(Z, bd, states, x, y, partial, lists, chunks, stream, idle, bad);
   }
 }
 
@@ -1996,8 +2120,12 @@ int r3m_retrieved_matvec(r3m_ctx ctx, const r3m_store* Z, const r3m_batch* batch
     R3M_REQUIRE(work_dev, R3M_ERR_INVALID_ARG, "work is NULL");
     // the retrieval index of this codebook (near lists), unless the caller
     // declares the one in the workspace current
+    int* bad = nullptr;
     if (!(batch->flags & R3M_BATCH_INDEX_READY)) {
-      check_states(bd, batch->states, Z->n_states, deferred_word(ctx), kDeferredBadState, stream);
+      if (dense_direct(Z, bd))
+        bad = deferred_word(ctx);  // the product itself looks at every state
+      else
+        check_states(bd, batch->states, Z->n_states, deferred_word(ctx), kDeferredBadState, stream);
       build_near_lists(Z, bd, batch->states, workspace_lists(work_dev, bd, Z), stream);
     }
     // first C128 call on this (store, batch): tune the group count on this x
@@ -2019,7 +2147,7 @@ int r3m_retrieved_matvec(r3m_ctx ctx, const r3m_store* Z, const r3m_batch* batch
       tuned_groups(ctx, Z, bd, batch->states, xs, y_dev, work_dev, workspace_lists(work_dev, bd, Z), stream);
     }
     launch_matvec(ctx, Z, bd, batch->states, vec_dtype, x_dev, y_dev, work_dev, nullptr, plan_groups(ctx, Z, bd),
-                  stream);
+                  stream, nullptr, bad);
   });
 }
 
@@ -2145,10 +2273,14 @@ extern "C" int r3m_retrieved_matvec_static(r3m_ctx ctx, const r3m_store* Z, cons
     }
     point_batch(&bd, sc.ptr);
     char* work = (char*)sc.ptr + head;
+    int* bad = nullptr;
     if (!(batch->flags & R3M_BATCH_INDEX_READY)) {
-      check_states(bd, batch->states, Z->n_states, deferred_word(ctx), kDeferredBadState, stream);
+      if (dense_direct(Z, bd))
+        bad = deferred_word(ctx);  // the product itself looks at every state
+      else
+        check_states(bd, batch->states, Z->n_states, deferred_word(ctx), kDeferredBadState, stream);
       build_near_lists(Z, bd, batch->states, workspace_lists(work, bd, Z), stream);
     }
-    launch_matvec(ctx, Z, bd, batch->states, vec_dtype, x_dev, y_dev, work, nullptr, groups, stream);
+    launch_matvec(ctx, Z, bd, batch->states, vec_dtype, x_dev, y_dev, work, nullptr, groups, stream, nullptr, bad);
   });
 }

@@ -63,14 +63,16 @@ size_t near_lists_bytes(const r3m_store* Z, const BatchDesc& bd);
 size_t near_lists_bytes_bound(int n_states, const BatchDesc& bd);
 void build_near_lists(const r3m_store* Z, const BatchDesc& bd, const uint8_t* states, void* lists_dev,
                       hipStream_t stream);
-// y (C128 or C64 vectors); lists NULL: the ones inside partial.  idle
+// y (C128 or C64 vectors); lists NULL: the ones inside partial.  bad
+// (nullable, all-dense stores on the direct product): set to
+// kDeferredBadState for a state byte >= n_states.  idle
 // (device, nullable, one int per right-hand side): the output of a right-hand
 // side b with idle[b] != 0 is not computed and keeps whatever it held (the
 // vector-unit far tiles, the reduction and every spectral pass skip it; the
 // matrix-core near items, which mix right-hand sides, still run)
 void launch_matvec(r3m_ctx ctx, const r3m_store* Z, const BatchDesc& bd, const uint8_t* states,
                    r3m_dtype vec_dtype, const void* x, void* y, void* partial, const void* lists, int chunks,
-                   hipStream_t stream, const int* idle = nullptr);
+                   hipStream_t stream, const int* idle = nullptr, int* bad = nullptr);
 // xs already in the store precision; y C128.  live (device, nullable): the
 // kernels return at once when *live == 0 (used to skip Arnoldi steps after
 // every right-hand side has converged); idle as above
