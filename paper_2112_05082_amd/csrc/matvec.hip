@@ -688,12 +688,14 @@ __global__ void __launch_bounds__(256) zero_ints_kernel(int* __restrict__ p, int
 
 // Block (slot d, chunk of 256 observer units, RHS): the classes of its pairs
 // are counted in LDS first, then one global atomic per class present.
-// pass 0: class counts; pass 1: pair placement at offsets[c] + cursor[c] + rank.
+// pass 0: class counts (and, with bad, kDeferredBadState set in it for a state
+// byte >= n_states); pass 1: pair placement at offsets[c] + cursor[c] + rank.
 // Dynamic LDS: 2 S (S + 1) ints.
 __global__ void __launch_bounds__(256)
 near_classify_kernel(const RhsDev* __restrict__ rhs, const uint8_t* __restrict__ states, int n_states, int Nx,
                      int Ny, int chunks, int* __restrict__ counts, int* __restrict__ cursor,
-                     const int* __restrict__ offsets, NearPair* __restrict__ pairs, int pass) {
+                     const int* __restrict__ offsets, NearPair* __restrict__ pairs, int pass,
+                     int* __restrict__ bad) {
   extern __shared__ int cl_lds[];
   const int S = n_states, SS = S * (S + 1);
   int* local = cl_lds;       // per-class count in this block
@@ -711,7 +713,9 @@ near_classify_kernel(const RhsDev* __restrict__ rhs, const uint8_t* __restrict__
     const int jx = ix - dx, jy = iy - dy;
     const bool valid = jx >= 0 && jx < R.Lx && jy >= 0 && jy < R.Ly;
     const int64_t j = (int64_t)jy * R.Lx + jx;
-    const int a = min((int)states[R.state_off + u], S - 1);
+    const int raw = states[R.state_off + u];
+    if (bad && slot == 0 && raw >= S) atomicOr(bad, kDeferredBadState);
+    const int a = min(raw, S - 1);
     const int bs = valid ? min((int)states[R.state_off + j], S - 1) : S;
     lc = a * (S + 1) + bs;
     rank = atomicAdd(&local[lc], 1);
@@ -1527,6 +1531,41 @@ int max_groups(const BatchDesc& bd) { return std::min(128, 4 * choose_chunks(bd,
 
 static bool store_has_far(const r3m_store* Z) { return Z->near_radius < std::max(Z->Dx, Z->Dy); }
 
+// The untuned displacement-group count.  All far workgroups of a launch cost
+// about the same (their share of the displacements plus a start worth
+// kFarStart of them), and the chip holds a fixed number at a time: for equal
+// arrays the count is the one whose last round of workgroups is full (2-bit
+// 32x32: 48 groups, 768 workgroups, 123 us; 64 groups, 1,024 workgroups, the
+// former default, 145; 96 groups 127); where the arrays differ the rounds
+// blur, and smaller workgroups shorten the end (20x20 to 32x32 x 12: 7 groups
+// 1,038 us, 16 793, 28 794).
+constexpr int kFarStart = 3;
+static int default_groups(const r3m_store* Z, const BatchDesc& bd) {
+  if (!store_has_far(Z) || bd.n_tiles == 0) return choose_chunks(bd, 64);
+  const double slots = 256.0 * (Z->near_dtype == R3M_C64 && Z->n / Z->n_states == 40 ? R3M_FAR_WAVES_PER_EU_F32
+                                                                                     : R3M_FAR_WAVES_PER_EU_F64);
+  // displacements of a tile, over all tiles (kBW x kBH units each) and at most
+  double work = 0.0, most = 0.0;
+  bool equal = true;
+  for (int b = 0; b < bd.B; ++b) {
+    const double nd = (double)(bd.Lx[b] + kBW - 1) * (bd.Ly[b] + kBH - 1);
+    work += nd * ((bd.Lx[b] + kBW - 1) / kBW) * ((bd.Ly[b] + kBH - 1) / kBH);
+    most = std::max(most, nd);
+    equal = equal && bd.Lx[b] == bd.Lx[0] && bd.Ly[b] == bd.Ly[0];
+  }
+  int best = 1;
+  double best_t = 1e300;
+  for (int g = 1; g <= max_groups(bd); ++g) {
+    const double wgs = (double)bd.n_tiles * g, one = most / g + kFarStart;
+    const double t = equal ? std::ceil(wgs / slots) * one : (work + wgs * kFarStart) / slots + 0.5 * one;
+    if (t < best_t) {
+      best_t = t;
+      best = g;
+    }
+  }
+  return best;
+}
+
 static int near_count(const r3m_store* Z) {
   const int Nx = std::min(Z->near_radius, Z->Dx), Ny = std::min(Z->near_radius, Z->Dy);
   return (2 * Nx + 1) * (2 * Ny + 1);
@@ -1621,7 +1660,7 @@ size_t near_lists_bytes_bound(int n_states, const BatchDesc& bd) {
 
 // builds the near retrieval lists of (batch, codebook states) at lists_dev
 void build_near_lists(const r3m_store* Z, const BatchDesc& bd, const uint8_t* states, void* lists_dev,
-                      hipStream_t stream) {
+                      hipStream_t stream, int* bad) {
   if (!near_on_mfma(Z) || dense_direct(Z, bd)) return;
   NearLists L = near_lists((char*)lists_dev, Z, bd);
   const int Nx = std::min(Z->near_radius, Z->Dx), Ny = std::min(Z->near_radius, Z->Dy);
@@ -1631,11 +1670,11 @@ void build_near_lists(const r3m_store* Z, const BatchDesc& bd, const uint8_t* st
   const dim3 grid((unsigned)(chunks * near_count(Z)), bd.B);
   const size_t lds = (size_t)2 * Z->n_states * (Z->n_states + 1) * sizeof(int);
   hipLaunchKernelGGL(near_classify_kernel, grid, dim3(256), lds, stream, bd.rhs, states, Z->n_states, Nx, Ny,
-                     chunks, L.counts, L.cursor, (const int*)L.offsets, L.pairs, 0);
+                     chunks, L.counts, L.cursor, (const int*)L.offsets, L.pairs, 0, bad);
   hipLaunchKernelGGL(near_scan_kernel, dim3(1), dim3(1024), 0, stream, (const int*)L.counts, L.n_cls, L.offsets,
                      L.cursor, L.items, L.n_items);
   hipLaunchKernelGGL(near_classify_kernel, grid, dim3(256), lds, stream, bd.rhs, states, Z->n_states, Nx, Ny,
-                     chunks, L.counts, L.cursor, (const int*)L.offsets, L.pairs, 1);
+                     chunks, L.counts, L.cursor, (const int*)L.offsets, L.pairs, 1, (int*)nullptr);
   R3M_CHECK_HIP(hipGetLastError());
 }
 
@@ -1919,7 +1958,7 @@ int tuned_groups(r3m_ctx ctx, const r3m_store* Z, const BatchDesc& bd, const uin
   const std::vector<int64_t> key = tune_key(Z, bd);
   auto it = ctx->tuned_groups.find(key);
   if (it != ctx->tuned_groups.end()) return it->second;
-  const int g0 = choose_chunks(bd, 64), gcap = max_groups(bd);
+  const int g0 = default_groups(Z, bd), gcap = max_groups(bd);
   // R3M_FAR_KERNEL ("valu" or "mfma") restricts the far kernel and
   // R3M_MATVEC_GROUPS fixes the count (clamped to [1, gcap]); used by tests and
   // to hold the launch shape constant across profiler runs
@@ -2051,7 +2090,7 @@ int plan_groups(r3m_ctx ctx, const r3m_store* Z, const BatchDesc& bd) {
   const std::vector<int64_t> key = tune_key(Z, bd);
   auto it = ctx->tuned_groups.find(key);
   if (it != ctx->tuned_groups.end()) return it->second;
-  return store_is_spectral(Z) ? spectral_default_plan(Z, bd.B) : choose_chunks(bd, 64);
+  return store_is_spectral(Z) ? spectral_default_plan(Z, bd.B) : default_groups(Z, bd);
 }
 
 bool plan_valid(const r3m_store* Z, const BatchDesc& bd, int plan) {
@@ -2122,11 +2161,12 @@ int r3m_retrieved_matvec(r3m_ctx ctx, const r3m_store* Z, const r3m_batch* batch
     // declares the one in the workspace current
     int* bad = nullptr;
     if (!(batch->flags & R3M_BATCH_INDEX_READY)) {
+      // the direct product and the lists look at every state byte themselves
       if (dense_direct(Z, bd))
-        bad = deferred_word(ctx);  // the product itself looks at every state
-      else
+        bad = deferred_word(ctx);
+      else if (!near_on_mfma(Z))
         check_states(bd, batch->states, Z->n_states, deferred_word(ctx), kDeferredBadState, stream);
-      build_near_lists(Z, bd, batch->states, workspace_lists(work_dev, bd, Z), stream);
+      build_near_lists(Z, bd, batch->states, workspace_lists(work_dev, bd, Z), stream, deferred_word(ctx));
     }
     // first C128 call on this (store, batch): tune the group count on this x
     // (the tuner writes y as C128, so C64 vectors take the tuned or default value)
@@ -2259,7 +2299,7 @@ extern "C" int r3m_retrieved_matvec_static(r3m_ctx ctx, const r3m_store* Z, cons
     std::vector<char> host;
     describe_batch(batch, kBW, kBH, &bd, host);
     const size_t head = (host.size() + 255) / 256 * 256;
-    const int groups = choose_chunks(bd, 64);
+    const int groups = default_groups(Z, bd);
     const size_t need = head + matvec_partial_bytes(bd, Z, max_groups(bd));
     R3M_REQUIRE(need <= (size_t)R3M_STATIC_SCRATCH_BYTES, R3M_ERR_BUFFER_TOO_SMALL,
                 "batch needs " + std::to_string(need) + " bytes of scratch; the static scratch holds " +
@@ -2275,11 +2315,12 @@ extern "C" int r3m_retrieved_matvec_static(r3m_ctx ctx, const r3m_store* Z, cons
     char* work = (char*)sc.ptr + head;
     int* bad = nullptr;
     if (!(batch->flags & R3M_BATCH_INDEX_READY)) {
+      // the direct product and the lists look at every state byte themselves
       if (dense_direct(Z, bd))
-        bad = deferred_word(ctx);  // the product itself looks at every state
-      else
+        bad = deferred_word(ctx);
+      else if (!near_on_mfma(Z))
         check_states(bd, batch->states, Z->n_states, deferred_word(ctx), kDeferredBadState, stream);
-      build_near_lists(Z, bd, batch->states, workspace_lists(work, bd, Z), stream);
+      build_near_lists(Z, bd, batch->states, workspace_lists(work, bd, Z), stream, deferred_word(ctx));
     }
     launch_matvec(ctx, Z, bd, batch->states, vec_dtype, x_dev, y_dev, work, nullptr, groups, stream, nullptr, bad);
   });

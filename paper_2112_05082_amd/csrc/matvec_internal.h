@@ -61,8 +61,9 @@ size_t matvec_partial_bytes(const BatchDesc& bd, const r3m_store* Z, int chunks)
 size_t partials_and_x_bytes(const BatchDesc& bd, const r3m_store* Z, int chunks);
 size_t near_lists_bytes(const r3m_store* Z, const BatchDesc& bd);
 size_t near_lists_bytes_bound(int n_states, const BatchDesc& bd);
+// (bad, nullable: set to kDeferredBadState for a state byte >= n_states)
 void build_near_lists(const r3m_store* Z, const BatchDesc& bd, const uint8_t* states, void* lists_dev,
-                      hipStream_t stream);
+                      hipStream_t stream, int* bad = nullptr);
 // y (C128 or C64 vectors); lists NULL: the ones inside partial.  bad
 // (nullable, all-dense stores on the direct product): set to
 // kDeferredBadState for a state byte >= n_states.  idle

@@ -84,3 +84,30 @@ def test_bad_state_is_reported():
         r3m.r3m_ctx_check(ctx)
     r3m.r3m_ctx_check(ctx)  # cleared
     ctx.close()
+
+
+@pytest.mark.parametrize("L", [3, 8, 17])
+def test_bad_state_is_reported_by_the_lists(L):
+    """Compressed stores check the states while they build their lists."""
+    from paper_2112_05082_amd import pipeline, r3m
+    from gpu_common import FREQ, unit
+    dev = "cuda:0"
+    ctx = r3m.Context(0)
+    geom = r3m.UnitGeom.from_macro(unit(1), FREQ, 1)
+    st = pipeline.compressed_store(ctx, geom, L, 1, r3m.C64, r3m.C64, 1e-3, 12, dev)
+    states = torch.zeros(2 * L * L, dtype=torch.uint8, device=dev)
+    batch = r3m.Batch([(L, L), (L, L)], [0, L * L], [0, L * L], states)
+    x = torch.ones(2 * L * L * 40, dtype=torch.complex64, device=dev)
+    y = torch.zeros_like(x)
+    work = torch.empty(r3m.matvec_work_bytes(ctx, st, batch, r3m.C64), dtype=torch.uint8, device=dev)
+    for at, bad in ((None, False), (2 * L * L - 1, True), (0, True)):
+        states.zero_()
+        if at is not None:
+            states[at] = 2
+        r3m.r3m_retrieved_matvec(ctx, st, batch, r3m.C64, x, y, work)
+        if bad:
+            with pytest.raises(r3m.R3MError):
+                r3m.r3m_ctx_check(ctx)
+        r3m.r3m_ctx_check(ctx)
+    assert r3m.matvec_groups(ctx, st, batch) >= 1
+    ctx.close()
