@@ -900,24 +900,62 @@ spec_product_kernel(const C2<T>* __restrict__ Zh, const C2<T>* __restrict__ Xh, 
   const int64_t kz = TR ? mirror_freq(k, lgGx, lgGy) : k;
   const C2<T>* xr = Xh + (size_t)b0 * n * K + k;
   const int mt = min(MT, n - m0);
-  constexpr int kUnroll = MT * BC <= 4 ? 4 : 2;
-#pragma unroll kUnroll
-  for (int c = 0; c < n; ++c) {
-    C2<T> zv[MT], xv[BC];
+  auto load = [&](int c, C2<T> (&zv)[MT], C2<T> (&xv)[BC]) {
 #pragma unroll
     for (int i = 0; i < MT; ++i)
       zv[i] = i < mt ? Zh[(TR ? (size_t)c * n + m0 + i : (size_t)(m0 + i) * n + c) * K + kz] : C2<T>{0, 0};
 #pragma unroll
     for (int q = 0; q < BC; ++q) xv[q] = q < nb ? xr[((size_t)q * n + c) * K] : C2<T>{0, 0};
+  };
+  if constexpr (sizeof(T) == 8) {
+    // four columns at a time, in the order of the FP64 matrix-core kernel: its
+    // 16x16x4 instruction adds its four products one after the other, each
+    // fused (measured bit for bit on random operands), so both kernels give
+    // the same bits and the batch's width may choose between them
+    constexpr int CB = 4;
+    for (int c0 = 0; c0 < n; c0 += CB) {
+      C2<T> zv[CB][MT], xv[CB][BC];
 #pragma unroll
-    for (int i = 0; i < MT; ++i)
+      for (int c = 0; c < CB; ++c) {
+        if (c0 + c < n) {
+          load(c0 + c, zv[c], xv[c]);
+        } else {
 #pragma unroll
-      for (int q = 0; q < BC; ++q) {
-        ar[i][q] = fma(zv[i].re, xv[q].re, ar[i][q]);
-        ar[i][q] = fma(-zv[i].im, xv[q].im, ar[i][q]);
-        ai[i][q] = fma(zv[i].re, xv[q].im, ai[i][q]);
-        ai[i][q] = fma(zv[i].im, xv[q].re, ai[i][q]);
+          for (int i = 0; i < MT; ++i) zv[c][i] = {0, 0};
+#pragma unroll
+          for (int q = 0; q < BC; ++q) xv[c][q] = {0, 0};
+        }
       }
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int q = 0; q < BC; ++q) {
+#pragma unroll
+          for (int c = 0; c < CB; ++c) ar[i][q] = fma(zv[c][i].re, xv[c][q].re, ar[i][q]);
+#pragma unroll
+          for (int c = 0; c < CB; ++c) ar[i][q] = fma(-zv[c][i].im, xv[c][q].im, ar[i][q]);
+#pragma unroll
+          for (int c = 0; c < CB; ++c) ai[i][q] = fma(zv[c][i].re, xv[c][q].im, ai[i][q]);
+#pragma unroll
+          for (int c = 0; c < CB; ++c) ai[i][q] = fma(zv[c][i].im, xv[c][q].re, ai[i][q]);
+        }
+    }
+  } else {
+    constexpr int kUnroll = MT * BC <= 4 ? 4 : 2;
+#pragma unroll kUnroll
+    for (int c = 0; c < n; ++c) {
+      C2<T> zv[MT], xv[BC];
+      load(c, zv, xv);
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int q = 0; q < BC; ++q) {
+          ar[i][q] = fma(zv[i].re, xv[q].re, ar[i][q]);
+          ar[i][q] = fma(-zv[i].im, xv[q].im, ar[i][q]);
+          ai[i][q] = fma(zv[i].re, xv[q].im, ai[i][q]);
+          ai[i][q] = fma(zv[i].im, xv[q].re, ai[i][q]);
+        }
+    }
   }
 #pragma unroll
   for (int i = 0; i < MT; ++i)
@@ -1228,6 +1266,7 @@ void launch_product(const C2<T>* Zh, const C2<T>* X, C2<T>* Y, int n, int64_t G2
   else
     hipLaunchKernelGGL((spec_product_kernel<T, MT, BC, false>), dim3((unsigned)nwg), dim3(256), 0, s, Zh, X, Y, n,
                        G2, B, n_mg, lgGx, lgGy, live, idle);
+  R3M_CHECK_HIP(hipGetLastError());
 }
 
 // The matrix-core product with KPW frequencies per wave and PC columns per
@@ -1264,45 +1303,57 @@ void launch_product_mfma(const C2<T>* Zh, const C2<T>* X, C2<T>* Y, int n, int64
   R3M_CHECK_HIP(hipGetLastError());
 }
 
+// complex128 batches on the vector units: up to two right-hand sides stream
+// the spectra faster than the matrix cores, whose 16-wide tiles are nearly
+// empty (us, matrix cores / vector units, one and two right-hand sides: 2-bit
+// 32x32 370 / 291, 373 / 319; 2-bit 12x12 118 / 87, 112 / 105; 1-bit 48x48 391
+// / 320, 393 / 346; three are even or slower, 410 / 463)
+constexpr int kSpecNarrow64 = 2;
 // Per-frequency product by plan (a valid spectral plan).  The vector-unit
 // kernel takes its register tile by batch width: 2 rows for one or two
 // right-hand sides (a stream of the spectra wants many waves in flight), 4
 // rows x 4 or 8 right-hand sides otherwise (arithmetic per load).  Every
 // matrix-core shape sums each output over the columns in the same order (16x16x4
 // tiles of four consecutive columns, in increasing column order), so all of
-// them give the same bits.
+// them give the same bits; in complex128 the vector-unit kernel does too, so a
+// batched product matches its single right-hand sides bit for bit.
 template <typename T>
 void product(const C2<T>* Zh, const C2<T>* X, C2<T>* Y, int n, int64_t G2, int B, bool tr, int lgGx, int lgGy,
              hipStream_t s, const int* live, const int* idle, int* tl, int plan) {
+  const int rf = spec_rhs_first(plan), lkg = spec_kt_groups(plan);
+#define R3M_VECTOR(MT, BC) return launch_product<T, MT, BC>(Zh, X, Y, n, G2, B, tr, lgGx, lgGy, s, live, idle)
+#define R3M_MATRIX(KPW, PC, RB) \
+  return launch_product_mfma<T, KPW, PC, RB>(Zh, X, Y, n, G2, B, tr, lgGx, lgGy, s, live, idle, tl, rf, lkg)
   if constexpr (sizeof(T) == 4) {
-    const C2<float>*zf = Zh, *xf = X;
-    C2<float>* yf = Y;
-    const int rf = spec_rhs_first(plan), lkg = spec_kt_groups(plan);
     switch (spec_shape(plan)) {
-      case 1: return launch_product_mfma<float, 1, 4, 1>(zf, xf, yf, n, G2, B, tr, lgGx, lgGy, s, live, idle, tl, rf, lkg);
-      case 2: return launch_product_mfma<float, 2, 4, 1>(zf, xf, yf, n, G2, B, tr, lgGx, lgGy, s, live, idle, tl, rf, lkg);
-      case 3: return launch_product_mfma<float, 2, 8, 1>(zf, xf, yf, n, G2, B, tr, lgGx, lgGy, s, live, idle, tl, rf, lkg);
-      case 4: return launch_product_mfma<float, 4, 4, 1>(zf, xf, yf, n, G2, B, tr, lgGx, lgGy, s, live, idle, tl, rf, lkg);
-      case 5: return launch_product_mfma<float, 1, 8, 1>(zf, xf, yf, n, G2, B, tr, lgGx, lgGy, s, live, idle, tl, rf, lkg);
-      case 6: return launch_product_mfma<float, 2, 4, 2>(zf, xf, yf, n, G2, B, tr, lgGx, lgGy, s, live, idle, tl, rf, lkg);
-      case 7: return launch_product_mfma<float, 1, 8, 2>(zf, xf, yf, n, G2, B, tr, lgGx, lgGy, s, live, idle, tl, rf, lkg);
+      case 1: R3M_MATRIX(1, 4, 1);
+      case 2: R3M_MATRIX(2, 4, 1);
+      case 3: R3M_MATRIX(2, 8, 1);
+      case 4: R3M_MATRIX(4, 4, 1);
+      case 5: R3M_MATRIX(1, 8, 1);
+      case 6: R3M_MATRIX(2, 4, 2);
+      case 7: R3M_MATRIX(1, 8, 2);
       default: break;
     }
+    if (B == 1) R3M_VECTOR(2, 1);
+    if (B == 2) R3M_VECTOR(2, 2);
+    if (B <= 4) R3M_VECTOR(4, 4);
+    R3M_VECTOR(4, 8);
   } else {
-    // complex128 spectra: the FP64 matrix cores at every batch width (one
-    // summation order per output, so a batched product matches its single
-    // right-hand sides bit for bit)
-    return launch_product_mfma<double, 1, 4, 1>(Zh, X, Y, n, G2, B, tr, lgGx, lgGy, s, live, idle, tl,
-                                                 spec_rhs_first(plan), spec_kt_groups(plan));
+    if (B > kSpecNarrow64) R3M_MATRIX(1, 4, 1);
+    // one row per thread where two would leave too few workgroups (2-bit 12x12,
+    // 320 of them: 87 us against 90; 1-bit 16x16, 160: 18 against 21, two
+    // right-hand sides 21 against 24), else two (2-bit 32x32: 291 against 301)
+    const int64_t wg2 = (G2 + 63) / 64 * ((n + 7) / 8);
+    if (B == 1) {
+      if (wg2 < 512) R3M_VECTOR(1, 1);
+      R3M_VECTOR(2, 1);
+    }
+    if (wg2 < 256) R3M_VECTOR(1, 2);
+    R3M_VECTOR(2, 2);
   }
-  if (B == 1)
-    launch_product<T, 2, 1>(Zh, X, Y, n, G2, B, tr, lgGx, lgGy, s, live, idle);
-  else if (B == 2)
-    launch_product<T, 2, 2>(Zh, X, Y, n, G2, B, tr, lgGx, lgGy, s, live, idle);
-  else if (B <= 4)
-    launch_product<T, 4, 4>(Zh, X, Y, n, G2, B, tr, lgGx, lgGy, s, live, idle);
-  else
-    launch_product<T, 4, 8>(Zh, X, Y, n, G2, B, tr, lgGx, lgGy, s, live, idle);
+#undef R3M_VECTOR
+#undef R3M_MATRIX
 }
 
 // relaxed compaction: y[u][r] = sum over states s of ymacro[u][s n_a + r]

@@ -83,3 +83,45 @@ def test_matvec_two_pass_lengths(L, D):
     assert np.abs(got["c64", False] - ref).max() <= 5e-6 * np.abs(ref).max()
     assert np.array_equal(got["c64", False], got["c64", True])
     ctx.close()
+
+
+@pytest.mark.parametrize("n_a,S,L,common", [(40, 2, 3, 0), (40, 4, 5, 0), (64, 1, 9, 0), (40, 2, 17, 3), (40, 4, 33, 0)])
+def test_c128_product_independent_of_width(n_a, S, L, common):
+    """One and two right-hand sides run on the vector units, more on the matrix
+    cores: the same bits, forward and (isolated units) transposed."""
+    from paper_2112_05082_amd import r3m
+    dev, n, D = "cuda:0", n_a * S + common, L - 1
+    ctx = r3m.Context(0)
+    g = torch.Generator(dev).manual_seed(L)
+    spec = torch.randn(r3m.spectral_bytes(n, D, D, r3m.SPEC_C128) // 8, dtype=torch.float64, device=dev, generator=g)
+    near = torch.randn((1, n, n), dtype=torch.complex128, device=dev, generator=g)
+    ext = torch.arange(common, dtype=torch.int32, device=dev) % 3 if common else None
+    store = r3m.Store(n, S, D, D, 0, r3m.C128, near, r3m.SPEC_C128, spec, common_ext=ext)
+    per = n_a + common
+    rng = np.random.default_rng(L)
+    books = [rng.integers(0, S, L * L).astype(np.uint8) for _ in range(5)]
+    x = torch.randn(5 * L * L * per, dtype=torch.complex128, device=dev, generator=g)
+    w = torch.rand((5 * L * L, S), dtype=torch.float64, device=dev, generator=g)
+    ref = {}
+    for width in (5, 1, 2):
+        for first in range(0, 5 - width + 1, 2):
+            ids = list(range(first, first + width))
+            batch = r3m.Batch.from_codebooks([books[i] for i in ids], [L] * width, dev)
+            xs = x[first * L * L * per:(first + width) * L * L * per].contiguous()
+            work = torch.empty(r3m.matvec_work_bytes(ctx, store, batch, r3m.C128), dtype=torch.uint8, device=dev)
+            out = [torch.zeros_like(xs)]
+            r3m.r3m_retrieved_matvec(ctx, store, batch, r3m.C128, xs, out[0], work)
+            if not common:
+                ws = w[first * L * L:(first + width) * L * L].contiguous()
+                work = torch.empty(r3m.relaxed_work_bytes(ctx, store, batch), dtype=torch.uint8, device=dev)
+                for tr in (False, True):
+                    out.append(torch.zeros_like(xs))
+                    r3m.r3m_relaxed_matvec(ctx, store, batch, ws, r3m.C128, xs, out[-1], work, transpose=tr)
+            for k, y in enumerate(out):
+                y = y.cpu().numpy().reshape(width, -1)
+                for i, row in zip(ids, y):
+                    if width == 5:
+                        ref[k, i] = row
+                    else:
+                        assert np.array_equal(row, ref[k, i])
+    ctx.close()
