@@ -32,7 +32,9 @@ constexpr int kSpecShapeCount = (int)(sizeof(kSpecShapes) / sizeof(kSpecShapes[0
 constexpr int kSpecRhsFirst = 8;  // default ordering threshold
 // the default threshold of a shape: workgroups of two 16-RHS tiles keep the
 // contiguous order up to 64 live tiles (measured on the 1,536-RHS solve:
-// 7.29, 7.17, 7.13, 7.10 s at 8, 24, 40, 64; 7.81 s never RHS tile first)
+// 7.29, 7.17, 7.13, 7.10 s at 8, 24, 40, 64; 7.81 s never RHS tile first).
+// The streamed kernel, which takes that shape's wide batches where the store's
+// rows fill its tiles, has one order and leaves the threshold unused
 inline int spec_default_rf(int shape) { return kSpecShapes[shape].rb == 2 ? 64 : kSpecRhsFirst; }
 inline int spec_plan(int shape, int rhs_first) { return kPlanSpectral | shape | rhs_first << 4; }
 inline int spec_shape(int plan) { return plan & 15; }

@@ -1225,6 +1225,213 @@ spec_product_mfma_kernel(const C2<T>* __restrict__ Zh, const C2<T>* __restrict__
   (void)LNB;
 }
 
+// The complex64 product of wide batches, streamed: the same tiles, fragments
+// and order of sums as above (the same bits), for n a multiple of 16.  One
+// persistent workgroup of 8 waves per CU owns 8 frequencies x 80 rows x 64
+// right-hand sides; wave w takes frequencies 2 (w % 4), +1 of all five row
+// tiles and RHS tiles 2 (w / 4), +1.  Chunks of four columns (20 KB of the
+// spectra, 16 KB of X) go from global memory straight to LDS, 16 bytes a lane,
+// into a ring of four 36 KB stages: three chunks (108 KB a CU) are in flight
+// under the one being multiplied, also over the end of a tile, and one barrier
+// a chunk says both that its stage is filled (each wave has waited for its own
+// loads) and that the stage of the chunk before is free for the next loads.
+// A stage holds rows [c][m] and [c][b] of 64 bytes (8 frequencies), the
+// 16-byte pair of frequencies f of row r in slot f ^ (r / 4) % 4: what 4 lanes
+// load is one 64-byte run, and the 16 lanes of a fragment (rows r, one pair)
+// read 16 different 16-byte bank groups.  Results leave through the stage of
+// the tile's last chunk, 16 rows x 32 right-hand sides at a time, as 64-byte
+// runs.
+// us against the kernel above at {2, 4, 2} (its faster order): 1-bit 64x64,
+// 1536 right-hand sides 12,470 / 13,460 (103 of the 154 TFLOP/s that a large
+// FP32 product reaches; without the results' stores it takes 10,450, without
+// the matrix instructions 10,530), 1-bit 32x32, 256 532 / 613, 64 164 / 172,
+// 1-bit 16x16, 512 270 / 317, 2-bit 32x32, 128 954 / 1064.  Slower were: a wave
+// per RHS tile with whole 64-byte runs (14,000: the accumulators no longer stay
+// in place), 16-byte stores from the registers (21,100), nontemporal X loads
+// (15,600) and stores (12,850).
+// The items are taken in the contiguous order only: RHS tile first took 13,080
+// against 12,730.
+constexpr int kSR = 64;                                  // right-hand sides of a workgroup
+constexpr int kStZ = 4 * kPM * 64, kStage = kStZ + 4 * kSR * 64, kStages = 4;
+constexpr int kSYB = 16 * 64 + 16;                       // bytes of a right-hand side's output rows, padded
+static_assert(2 * kPB * kSYB <= kStage, "the output tile fits a stage");
+// 16 bytes a lane from base + off (off by lane) to LDS bytes lds + 16 lane.  No
+// register is written; wait_loads of the same wave and a barrier make the bytes
+// visible.
+__device__ __forceinline__ void load_to_lds(const void* base, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds)
+               : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// every wave's LDS reads and writes so far are done
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+spec_product_stream_kernel(const C2<float>* __restrict__ Zh, const C2<float>* __restrict__ Xh,
+                           C2<float>* __restrict__ Yh, int n, int64_t K, int B, int n_mg, int n_bt,
+                           const int* __restrict__ live, const int* __restrict__ tile_list,
+                           const int* __restrict__ n_live) {
+  if (live && *live == 0) return;
+  extern __shared__ unsigned char smem_raw[];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int p = w & 3, h = w >> 2;  // frequency pair, half of the right-hand sides
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem_raw);
+  const int nl = tile_list ? *n_live : n_bt, nc = n / 4;
+  // items (frequency-tile pair, row group, RHS tile group, tile of the pair),
+  // an eighth for each XCD (workgroup id mod 8), its workgroups in turn
+  const uint32_t ng = (uint32_t)(nl + 3) / 4, items = (uint32_t)(K / 8) * n_mg * ng, eighth = (items + 7) / 8;
+  const uint32_t first = eighth * (blockIdx.x & 7), item_end = min(first + eighth, items), per_x = gridDim.x >> 3;
+  struct Tile {
+    int64_t k0;
+    int m0, b0[4];  // b0: first right-hand side of each RHS tile (-1: past the last)
+  };
+  // loads: the tile they are in, its next chunk, and of this wave the address
+  // of that chunk's first 1 KB run, the distance of the next, the lanes'
+  // offsets and the runs (waves 0..3: column w of the spectra's five row
+  // tiles; waves 4..7: the four columns of RHS tile w - 4)
+  Tile lt;
+  uint32_t item = first + (blockIdx.x >> 3) - per_x;
+  int l_chunk = 0;
+  bool more = true;
+  const char* l_base = nullptr;
+  int64_t l_step = 0;
+  uint32_t l_off = 0;
+  int l_last = 0;  // runs past this one repeat it (row tiles past n, never stored)
+  const uint32_t slot = (uint32_t)((lane & 3) ^ (lane >> 4)) * 16;
+  auto next_tile = [&] {
+    item += per_x;
+    if (item >= item_end) {
+      more = false;
+      return;
+    }
+    const uint32_t r0 = item >> 1, r1 = r0 / ng, bi = r0 - r1 * ng, r2 = r1 / (uint32_t)n_mg, mg = r1 - r2 * n_mg;
+    lt.k0 = ((int64_t)r2 * 2 + (item & 1)) * 8;
+    lt.m0 = (int)mg * kPM;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int ti = (int)bi * 4 + r;
+      lt.b0[r] = ti < nl ? (tile_list ? tile_list[ti] : ti) * kPB : -1;
+    }
+    l_chunk = 0;
+    int row = lane >> 2;
+    if (w < 4) {
+      l_base = (const char*)(Zh + ((int64_t)lt.m0 * n + w) * K + lt.k0);
+      l_step = (int64_t)16 * n * K * 8;
+      l_last = min(4, (n - lt.m0) / 16 - 1);
+    } else {
+      const int b = p == 0 ? lt.b0[0] : p == 1 ? lt.b0[1] : p == 2 ? lt.b0[2] : lt.b0[3];
+      const int bb = b >= 0 ? b : lt.b0[0];  // (a tile past the last repeats the first, never stored)
+      l_base = (const char*)(Xh + (int64_t)bb * n * K + lt.k0);
+      l_step = K * 8;
+      l_last = 3;
+      row = min(row, B - 1 - bb);
+    }
+    l_off = (uint32_t)((int64_t)row * n * K * 8) + slot;
+  };
+  int l_stage = 0, ahead = 0;  // stage of the next load; chunks loaded past the one being multiplied
+  auto load_chunk = [&] {
+    if (!more) return;
+    const uint32_t dst = lds0 + l_stage * kStage + (w < 4 ? w * (kPM * 64) : kStZ + p * 1024);
+    const uint32_t dst_step = w < 4 ? 1024 : kSR * 64;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) load_to_lds(l_base + min(i, l_last) * l_step, l_off, dst + i * dst_step);
+    if (w < 4) load_to_lds(l_base + l_last * l_step, l_off, dst + 4 * dst_step);
+    l_base += 4 * K * 8;
+    l_stage = (l_stage + 1) & 3;
+    ++ahead;
+    if (++l_chunk == nc) next_tile();
+  };
+  next_tile();
+  if (!more) return;
+  Tile ct = lt;
+#pragma unroll 1
+  for (int i = 0; i < 3; ++i) load_chunk();
+  --ahead;  // chunks past the first one
+  int stage = 0;
+  // lane offsets of the fragments' pairs and of the output rows
+  const uint32_t frag = (uint32_t)(lane & 15) * 64 + ((p ^ ((lane >> 2) & 3)) * 16);
+  const unsigned char* zf = smem_raw + (lane >> 4) * (kPM * 64) + frag;
+  const unsigned char* xf = smem_raw + kStZ + (lane >> 4) * (kSR * 64) + h * 2048 + frag;
+  const uint32_t y_off = (uint32_t)(lane >> 2) * (uint32_t)(K * 8) + (lane & 3) * 16;
+  for (;;) {
+    f32x4 are[2][5][2], aim[2][5][2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int t = 0; t < 5; ++t)
+#pragma unroll
+        for (int r = 0; r < 2; ++r) are[q][t][r] = aim[q][t][r] = f32x4{0, 0, 0, 0};
+    const int nr = h == 0 ? (ct.b0[1] >= 0 ? 2 : 1) : ct.b0[3] >= 0 ? 2 : ct.b0[2] >= 0 ? 1 : 0;
+    auto multiply = [&] {
+      const unsigned char *zs = zf + stage * kStage, *xs = xf + stage * kStage;
+      f32x4 av[5];
+#pragma unroll
+      for (int t = 0; t < 5; ++t) av[t] = *(const f32x4*)(zs + t * 1024);
+      f32x4 bw[2] = {*(const f32x4*)xs, *(const f32x4*)(xs + 1024)};
+      load_chunk();
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        if (nr <= r) break;  // uniform
+        const f32x4 bv = bw[r];
+#pragma unroll
+        for (int t = 0; t < 5; ++t)
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            are[q][t][r] = mfma_16x16x4(av[t][2 * q], bv[2 * q], are[q][t][r]);
+            are[q][t][r] = mfma_16x16x4(-av[t][2 * q + 1], bv[2 * q + 1], are[q][t][r]);
+            aim[q][t][r] = mfma_16x16x4(av[t][2 * q], bv[2 * q + 1], aim[q][t][r]);
+            aim[q][t][r] = mfma_16x16x4(av[t][2 * q + 1], bv[2 * q], aim[q][t][r]);
+          }
+      }
+    };
+    for (int c = 0; c < nc; ++c) {
+      // this wave's loads of the chunk: all but those of the two chunks after
+      // it (loads and stores complete in order; stores issued since only make
+      // the wait longer)
+      if (ahead < 2) wait_loads<0>();
+      else if (w < 4) wait_loads<10>();
+      else wait_loads<8>();
+      lds_barrier();
+      multiply();
+      if (c + 1 < nc) {
+        stage = (stage + 1) & 3;
+        --ahead;
+      }
+    }
+    unsigned char* ys = smem_raw + stage * kStage;
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      if (ct.b0[r] < 0) break;  // uniform (no tile of the second half either)
+#pragma unroll
+      for (int t = 0; t < 5; ++t) {
+        if (ct.m0 + t * 16 >= n) break;  // uniform
+        lds_barrier();  // the stage's last reads are done
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          *(f32x4*)(ys + (h * 16 + (lane & 15)) * kSYB + (4 * (lane >> 4) + i) * 64 + p * 16) =
+              f32x4{are[0][t][r][i], aim[0][t][r][i], are[1][t][r][i], aim[1][t][r][i]};
+        lds_barrier();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int b0 = ct.b0[(i >> 1) * 2 + r], b = b0 + w + 8 * (i & 1);
+          if (b0 >= 0 && b < B) {
+            char* dst = (char*)(Yh + ((int64_t)b * n + ct.m0 + t * 16) * K + ct.k0);
+            *(f32x4*)(dst + y_off) = *(const f32x4*)(ys + (w + 8 * i) * kSYB + lane * 16);
+          }
+        }
+      }
+    }
+    if (ahead == 0) return;  // no chunk of another tile was loaded
+    stage = (stage + 1) & 3;
+    --ahead;
+    ct = lt;
+  }
+}
+
 // The live tiles of the matrix-core product (tiles of kPB right-hand sides
 // with any idle[b] == 0) in increasing order, and their count: one workgroup,
 // thread t takes a contiguous run of tiles, a scan of the counts places them.
@@ -1303,6 +1510,41 @@ void launch_product_mfma(const C2<T>* Zh, const C2<T>* X, C2<T>* Y, int n, int64
   R3M_CHECK_HIP(hipGetLastError());
 }
 
+constexpr int kStreamWgs = 256;  // one per CU
+// wide batches on stores whose rows fill 16-row tiles; the lanes' offsets in
+// the grids of 16 rows or right-hand sides take 31 bits.  Below four RHS tiles
+// (1-bit 32x32, 64 right-hand sides: 164 us against 172) the workgroup's last
+// tiles would be empty.
+bool product_streams(int n, int64_t G2, int B, bool tr) {
+  const int64_t n_bt = (B + kPB - 1) / kPB;
+  return !tr && n % 16 == 0 && G2 >= 16 && n_bt >= 4 && (int64_t)16 * n * G2 * 8 < ((int64_t)1 << 31) &&
+         G2 / 8 * ((n + kPM - 1) / kPM) * ((n_bt + 3) / 4) < ((int64_t)1 << 31) - 8 * kStreamWgs;
+}
+// tl: room for the live-tile list (ceil(B / 16) + 1 ints), used with idle flags
+void launch_product_stream(const C2<float>* Zh, const C2<float>* X, C2<float>* Y, int n, int64_t G2, int B,
+                           hipStream_t s, const int* live, const int* idle, int* tl) {
+  const int n_mg = (n + kPM - 1) / kPM, n_bt = (B + kPB - 1) / kPB;
+  if (idle) {
+    hipLaunchKernelGGL(live_tiles_kernel, dim3(1), dim3(1024), 0, s, idle, B, n_bt, tl, tl + n_bt);
+    R3M_CHECK_HIP(hipGetLastError());
+  }
+  // the LDS limit, raised once per device as for the fused transforms
+  static std::atomic<uint64_t> raised{0};
+  int dev = 0;
+  R3M_CHECK_HIP(hipGetDevice(&dev));
+  const uint64_t bit = (uint64_t)1 << (dev & 63);
+  if (!(raised.load() & bit)) {
+    R3M_CHECK_HIP(hipFuncSetAttribute((const void*)spec_product_stream_kernel,
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, kStages * kStage));
+    raised.fetch_or(bit);
+  }
+  const int64_t items = G2 / 8 * n_mg * ((n_bt + 3) / 4);
+  const int64_t nwg = std::min<int64_t>((items + 7) / 8 * 8, kStreamWgs);
+  hipLaunchKernelGGL(spec_product_stream_kernel, dim3((unsigned)nwg), dim3(512), kStages * kStage, s, Zh, X, Y, n, G2,
+                     B, n_mg, n_bt, live, idle ? tl : nullptr, idle ? tl + n_bt : nullptr);
+  R3M_CHECK_HIP(hipGetLastError());
+}
+
 // complex128 batches on the vector units: up to two right-hand sides stream
 // the spectra faster than the matrix cores, whose 16-wide tiles are nearly
 // empty (us, matrix cores / vector units, one and two right-hand sides: 2-bit
@@ -1331,7 +1573,9 @@ void product(const C2<T>* Zh, const C2<T>* X, C2<T>* Y, int n, int64_t G2, int B
       case 3: R3M_MATRIX(2, 8, 1);
       case 4: R3M_MATRIX(4, 4, 1);
       case 5: R3M_MATRIX(1, 8, 1);
-      case 6: R3M_MATRIX(2, 4, 2);
+      case 6:
+        if (product_streams(n, G2, B, tr)) return launch_product_stream(Zh, X, Y, n, G2, B, s, live, idle, tl);
+        R3M_MATRIX(2, 4, 2);
       case 7: R3M_MATRIX(1, 8, 2);
       default: break;
     }
