@@ -1010,7 +1010,7 @@ constexpr int kZP = kPM + 1, kXP = kPB + 1;
 // complex128 frequency per 16-byte access.
 template <typename T, int KPW, int PC, int RB, bool TR>
 __global__ void __launch_bounds__(256)
-    __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 1
+    __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2
                                        : KPW == 2 && PC == 4 && RB == 1 ? 3 : KPW == 2 && RB == 2 ? 2
                                        : KPW == 1 && PC == 8 && RB == 2 ? 3 : 1)))
 spec_product_mfma_kernel(const C2<T>* __restrict__ Zh, const C2<T>* __restrict__ Xh, C2<T>* __restrict__ Yh,
@@ -1584,6 +1584,17 @@ void product(const C2<T>* Zh, const C2<T>* X, C2<T>* Y, int n, int64_t G2, int B
     if (B <= 4) R3M_VECTOR(4, 4);
     R3M_VECTOR(4, 8);
   } else {
+    // two RHS tiles per workgroup where there are two, as in complex64, in the
+    // contiguous order below 32 tiles (ms, contiguous / RHS tile first: 1-bit
+    // 64x64, 128 right-hand sides 2.39 / 4.41, 256 4.52 / 4.69, 512 9.25 / 9.43,
+    // 1024 20.97 / 17.79; 2-bit 32x32, 256 3.92 / 3.96, 512 8.79 / 7.63); one tile against two, us: 1-bit 48x48, 24 right-hand sides 788 /
+    // 648, 48 1226 / 1151, 2-bit 32x32 716 / 580, 1089 / 1000, 1-bit 64x64, 1536
+    // 35,170 / 27,410.  (Kept to two waves per SIMD, 158 registers instead of
+    // 144, one tile is faster too: 1-bit 48x48, 4
+    // right-hand sides 416 / 391, 2-bit 32x32, 16 492 / 468.)
+    if (B > kPB)
+      return launch_product_mfma<T, 1, 4, 2>(Zh, X, Y, n, G2, B, tr, lgGx, lgGy, s, live, idle, tl, std::max(rf, 32),
+                                             lkg);
     if (B > kSpecNarrow64) R3M_MATRIX(1, 4, 1);
     // one row per thread where two would leave too few workgroups (2-bit 12x12,
     // 320 of them: 87 us against 90; 1-bit 16x16, 160: 18 against 21, two

@@ -69,3 +69,32 @@ def test_solve_identical_with_stream():
     assert len(set(out[0][1])) >= 4 and out[0][1] == out[1][1]
     assert torch.equal(out[0][0], out[1][0])
     ctx.close()
+
+
+@pytest.mark.parametrize("n_a,S,D", [(40, 2, 1), (40, 2, 11), (64, 3, 3)])
+def test_c128_product_two_tiles(n_a, S, D):
+    """Complex128 products of more than 16 right-hand sides (two tiles per
+    workgroup: 17 and 32, then 33 and 130 with an unpaired and a ragged last
+    tile) equal those of 5 at a time bit for bit."""
+    from paper_2112_05082_amd import r3m
+    ctx = r3m.Context(0)
+    n, L = n_a * S, D + 1
+    g = torch.Generator(DEV).manual_seed(D)
+    spec = torch.randn(r3m.spectral_bytes(n, D, D, r3m.SPEC_C128) // 8, dtype=torch.float64, device=DEV, generator=g)
+    near = torch.randn((1, n, n), dtype=torch.complex128, device=DEV, generator=g)
+    store = r3m.Store(n, S, D, D, 0, r3m.C128, near, r3m.SPEC_C128, spec)
+    books = [np.random.default_rng(b).integers(0, S, L * L).astype(np.uint8) for b in range(130)]
+    x = torch.randn((130, L * L * n_a), dtype=torch.complex128, device=DEV, generator=g)
+
+    def product(first, count):
+        batch = r3m.Batch.from_codebooks(books[first:first + count], [L] * count, DEV)
+        xs = x[first:first + count].contiguous()
+        work = torch.empty(r3m.matvec_work_bytes(ctx, store, batch, r3m.C128), dtype=torch.uint8, device=DEV)
+        y = torch.zeros_like(xs)
+        r3m.r3m_retrieved_matvec(ctx, store, batch, r3m.C128, xs, y, work)
+        return y
+
+    ref = torch.cat([product(i, 5) for i in range(0, 130, 5)])
+    for count in (17, 32, 33, 130):
+        assert torch.equal(product(0, count), ref[:count])
+    ctx.close()
