@@ -234,17 +234,18 @@ __device__ __forceinline__ void store_entry(OutT* out, size_t idx, C128 v, doubl
 // its mirror image nslots - 1 - s (-d), tile pair (I, J).  1,024 threads, one
 // pair each; 147 KB of integrals and 11 KB of quadrature points in LDS, so one
 // workgroup (four waves per SIMD) per CU.  Points and integrals are stored
-// source-fastest: lanes read consecutive words.
+// source-fastest: lanes read consecutive words.  A launch takes the workgroups
+// from tile pair tp0 of slot slot0 on (see max_workgroups).
 template <typename OutT>
 __global__ void __launch_bounds__(kTilePairs)
 fill_far_kernel(GeomDev g, FillDev f, double k, double px, double py, int Dx, int Dy, int near_x, int near_y,
-                OutT* __restrict__ out, int* __restrict__ flag) {
+                int slot0, int tp0, OutT* __restrict__ out, int* __restrict__ flag) {
   extern __shared__ double2 far_lds[];
   double2* T = far_lds;                                                   // [9][kTilePairs]
   double* Po = reinterpret_cast<double*>(far_lds + 9 * kTilePairs);       // [7][3][kTileTri]
   double* Qo = Po + 21 * kTileTri;
   const int n_tp = f.n_tiles * f.n_tiles;
-  const int slot = blockIdx.x / n_tp, tp = blockIdx.x % n_tp;
+  const int id = tp0 + (int)blockIdx.x, slot = slot0 + id / n_tp, tp = id % n_tp;
   const int dx = slot % (2 * Dx + 1) - Dx, dy = slot / (2 * Dx + 1) - Dy;
   if (abs(dx) <= near_x && abs(dy) <= near_y) return;  // uniform: a near block
   const FillTile& I = f.tiles[tp / f.n_tiles];
@@ -574,12 +575,15 @@ void launch_fill(r3m_ctx ctx, const r3m_unit_geom* geom, const GeomDev& g, const
   const int near_x = (int)std::min<int64_t>(Dx, reach), near_y = (int)std::min<int64_t>(Dy, reach);
   const int64_t half = ((int64_t)(2 * Dx + 1) * (2 * Dy + 1) - 1) / 2;
   if (near_x < Dx || near_y < Dy) {
-    R3M_REQUIRE(half * n_tp < (int64_t)1 << 31, R3M_ERR_UNSUPPORTED, "too many displacement blocks");
     R3M_CHECK_HIP(hipFuncSetAttribute((const void*)fill_far_kernel<OutT>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                       (int)kFarLds));
-    hipLaunchKernelGGL(fill_far_kernel<OutT>, dim3((unsigned)(half * n_tp)), dim3(kTilePairs), kFarLds, stream, g, f,
-                       k, geom->period_x, geom->period_y, Dx, Dy, near_x, near_y, out, flag);
-    R3M_CHECK_HIP(hipGetLastError());
+    const int64_t all = half * n_tp, most = max_workgroups(kTilePairs);
+    for (int64_t w0 = 0; w0 < all; w0 += most) {
+      hipLaunchKernelGGL(fill_far_kernel<OutT>, dim3((unsigned)std::min(most, all - w0)), dim3(kTilePairs), kFarLds,
+                         stream, g, f, k, geom->period_x, geom->period_y, Dx, Dy, near_x, near_y, (int)(w0 / n_tp),
+                         (int)(w0 % n_tp), out, flag);
+      R3M_CHECK_HIP(hipGetLastError());
+    }
   }
   const int64_t units = (int64_t)(2 * near_x + 1) * (2 * near_y + 1) * n_tp;
   const size_t per = 9 * kTilePairs * sizeof(double2);

@@ -269,4 +269,10 @@ int guarded(r3m_ctx ctx, F&& f) {
 
 inline unsigned ceil_div(size_t a, size_t b) { return (unsigned)((a + b - 1) / b); }
 
+// Most workgroups of `threads` threads that one launch takes: a grid dimension
+// holds fewer than 2^32 threads, and a larger one wraps around without an
+// error, so that only its first workgroups run.  Rounded down to a multiple of
+// 8 (a workgroup's XCD is its id mod 8).
+inline int64_t max_workgroups(int threads) { return (((int64_t)1 << 32) - 1) / threads / 8 * 8; }
+
 }  // namespace r3m
