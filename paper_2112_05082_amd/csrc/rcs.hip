@@ -303,16 +303,17 @@ __device__ __forceinline__ void rcs_steps(const GeomDev& g, const int2* list, in
 // One workgroup per (RHS, unit chunk, 32 directions); the direction groups of
 // a chunk share one XCD (and its L2 copy of the currents).  partial (n_chunks
 // > 1): [chunk][b][dir][6]; else sigma is written.  FULL: n_a a multiple of 40
-// and no shared entries.
+// and no shared entries.  A launch takes the workgroups from id0 (a multiple of
+// 8) on (see max_workgroups).
 template <bool FULL>
 __global__ void __launch_bounds__(kRcsThreads, 2)
 rcs_kernel(GeomDev g, const RhsDev* __restrict__ rhs, const uint8_t* __restrict__ states,
            const double2* __restrict__ I, const double2* __restrict__ F, const double* __restrict__ rhat, int n_dir,
-           int n_a, int n_v, int n_states, int B, int n_dgrp, int n_chunks, int64_t chunk_units, double k, double px,
-           double py, double scale, double* __restrict__ partial, double* __restrict__ sigma) {
+           int n_a, int n_v, int n_states, int B, int n_dgrp, int n_chunks, int64_t chunk_units, int64_t id0, double k,
+           double px, double py, double scale, double* __restrict__ partial, double* __restrict__ sigma) {
   __shared__ int2 list_s[kRcsWaves][kRcsList];
   __shared__ double sum_s[kRcsWaves][6][kRcsDirs];
-  const int64_t id = blockIdx.x;
+  const int64_t id = id0 + blockIdx.x;
   const int64_t slot = id / 8, grp = (slot / n_dgrp) * 8 + id % 8;
   if (grp >= (int64_t)B * n_chunks) return;
   // chunk-major: the XCDs then share the arrays' first chunks and their last,
@@ -648,20 +649,22 @@ int r3m_rcs(r3m_ctx ctx, const r3m_unit_geom* geom, const r3m_batch* batch, cons
                        stream, g, (const double*)ddev, n_dir, k, F, rhat);
     const double scale = k * k * kEta0 * kEta0 / (4.0 * kPi) / (e0 * e0);
     check_states(bd, batch->states, geom->n_states, deferred_word(ctx), kDeferredBadState, stream);
-    const size_t n_wg = ((size_t)bd.B * n_chunks + 7) / 8 * 8 * n_dgrp;
-    R3M_REQUIRE(n_wg < (1ull << 31), R3M_ERR_INVALID_ARG,
-                "too many right-hand sides x directions for one RCS launch");
+    R3M_REQUIRE((size_t)ceil_div((size_t)bd.B, 8) * 8 * ceil_div((size_t)n_dir, 64) < (1ull << 31),
+                R3M_ERR_INVALID_ARG, "too many right-hand sides x directions for one RCS call");
+    const int64_t n_wg = ((int64_t)bd.B * n_chunks + 7) / 8 * 8 * n_dgrp, most = max_workgroups(kRcsThreads);
     auto launch = [&](auto kern) {
-      hipLaunchKernelGGL(kern, dim3((unsigned)n_wg), dim3(kRcsThreads), 0, stream, g, bd.rhs, batch->states,
-                         (const double2*)I_dev, (const double2*)F, (const double*)rhat, n_dir, n_a, vec_per_unit(geom),
-                         geom->n_states, bd.B, n_dgrp, n_chunks, chunk_units, k, geom->period_x, geom->period_y,
-                         scale, part, sigma_dev);
+      for (int64_t id0 = 0; id0 < n_wg; id0 += most) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)std::min(most, n_wg - id0)), dim3(kRcsThreads), 0, stream, g, bd.rhs,
+                           batch->states, (const double2*)I_dev, (const double2*)F, (const double*)rhat, n_dir, n_a,
+                           vec_per_unit(geom), geom->n_states, bd.B, n_dgrp, n_chunks, chunk_units, id0, k,
+                           geom->period_x, geom->period_y, scale, part, sigma_dev);
+        R3M_CHECK_HIP(hipGetLastError());
+      }
     };
     if (n_a % kRcsRows == 0 && vec_per_unit(geom) == n_a)
       launch(rcs_kernel<true>);
     else
       launch(rcs_kernel<false>);
-    R3M_CHECK_HIP(hipGetLastError());
     if (n_chunks > 1)
       hipLaunchKernelGGL(rcs_finish_kernel, dim3(ceil_div((size_t)bd.B * n_dir, 256)), dim3(256), 0, stream,
                          (const double*)part, (const double*)rhat, n_dir, bd.B, n_chunks, scale, sigma_dev);

@@ -33,3 +33,28 @@ def test_fill_of_more_blocks_than_one_launch_takes():
         ref = efie.displacement_block(unit, dx, dy, K, 1)[0, 0]
         assert abs(complex(out[dy + D, dx + D]) - ref) <= 2e-7 * abs(ref), (dx, dy)
     ctx.close()
+
+
+def test_rcs_of_more_workgroups_than_one_launch_takes():
+    """8,192 right-hand sides x 65,537 directions: 16,785,408 workgroups of 256 threads."""
+    from paper_2112_05082_amd import r3m
+    unit = macro_unit((0.006,), 1)
+    dev, B, n_dir = "cuda:0", 8192, 65537
+    ctx = r3m.Context(0)
+    geom = r3m.UnitGeom.from_macro(unit, FREQ, 1)
+    states = torch.zeros(1, dtype=torch.uint8, device=dev)
+    batch = r3m.Batch([(1, 1)] * B, list(range(B)), [0] * B, states)
+    I = torch.randn(B, dtype=torch.complex128, device=dev, generator=torch.Generator(dev).manual_seed(1))
+    t = np.linspace(-1.0, 1.0, n_dir)
+    dirs = np.stack([1.4 * t, 3.0 * t], 1)
+    sigma = torch.full((B, n_dir), float("nan"), dtype=torch.float64, device=dev)
+    r3m.r3m_rcs(ctx, geom, batch, I, dirs, 1.0, sigma)
+    # one basis: sigma is |I|^2 times the pattern of a unit current
+    one = torch.zeros(n_dir, dtype=torch.float64, device=dev)
+    r3m.r3m_rcs(ctx, geom, r3m.Batch([(1, 1)], [0], [0], states), torch.ones(1, dtype=torch.complex128, device=dev),
+                dirs, 1.0, one)
+    assert bool((one > 0).all())
+    for b in range(0, B, 512):
+        ref = I[b:b + 512].abs().square()[:, None] * one[None, :]
+        assert bool(((sigma[b:b + 512] - ref).abs() <= 1e-12 * ref).all()), b
+    ctx.close()
