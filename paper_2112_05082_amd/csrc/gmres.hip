@@ -480,20 +480,44 @@ finish_partials_kernel(const double2* __restrict__ partial, int maxP, int nvec, 
   if ((threadIdx.x & 63) == 0) out[(size_t)b * nvec + i] = t;
 }
 
-// the per-block parts of ||w||^2 summed once into out[b] (grid B)
+// The first Gram-Schmidt pass of a right-hand side suffices where it kept
+// ||w|| >= eta ||A v_j|| (with A v_j = sum_i H[i][j] V_i + w: ||w||^2 >= eta^2 /
+// (1 - eta^2) sum_i |H[i][j]|^2), the criterion of Kahan and Parlett: after one
+// projection the part of w left in the basis's span is of the order of the
+// rounding unit times ||A v_j||, at most 1/eta times the rounding unit
+// relative to ||w||.
+constexpr double kCgs2Eta = 0.1;
+
+// The per-block parts of ||w||^2 summed once into out[b] (grid B).  With H
+// (between the passes of a selective Gram-Schmidt step, nvec <= kFoldMaxVecEl)
+// out[b] is the decision instead: 1 where the first pass suffices, else 0.  It
+// is taken here, once per right-hand side: the second update adds to the
+// H[i][j] that it depends on, so that update's blocks could not each take it.
 __global__ void __launch_bounds__(256)
 finish_norm_kernel(const double* __restrict__ npart, int maxB, const RhsVec* __restrict__ rv,
                    double* __restrict__ out, const int* __restrict__ run_prev, const int* __restrict__ idle,
-                   int nsub) {
+                   int nsub, const double2* __restrict__ H, int m, int j, int nvec) {
   if (run_prev && *run_prev == 0) return;
   if (idle && idle[blockIdx.x]) return;
   __shared__ double2 sh[4];
+  __shared__ double h2[kFoldMaxVecEl];
   const int b = blockIdx.x;
   const int64_t nb = (rv[b].N + 64 * nsub - 1) / (64 * nsub);  // gs_update_kernel's blocks
+  if (H && threadIdx.x < nvec) {
+    const double2 h = H[(size_t)b * (m + 1) * m + (size_t)threadIdx.x * m + j];
+    h2[threadIdx.x] = h.x * h.x + h.y * h.y;
+  }
   double t = 0.0;
   for (int64_t q = threadIdx.x; q < nb; q += blockDim.x) t += npart[(size_t)b * maxB + q];
   const double2 s2 = block_sum2(make_double2(t, 0.0), sh);
-  if (threadIdx.x == 0) out[b] = s2.x;
+  if (threadIdx.x != 0) return;
+  if (!H) {
+    out[b] = s2.x;
+    return;
+  }
+  double hh = 0.0;
+  for (int i = 0; i < nvec; ++i) hh += h2[i];  // (written before block_sum2's barrier)
+  out[b] = s2.x >= kCgs2Eta * kCgs2Eta / (1.0 - kCgs2Eta * kCgs2Eta) * hh ? 1.0 : 0.0;
 }
 
 // w -= sum_{i<nvec} h_i V_i with h_i the sum of the partials of the preceding
@@ -649,14 +673,8 @@ gs_update_kernel(const VB* __restrict__ V, WB* __restrict__ w, const RhsVec* __r
 // stay in registers, each wave sums conj(V_i) w over its lanes
 // (wave_transpose_sum) and the block adds the waves in a fixed order into
 // partial2[b][i][block].  Same arguments and outputs as gs_update_kernel with
-// nsub = 4.  skip_nsum (nullable; a second pass, mode 1): ||w||^2 after the
-// first pass per RHS; the pass then leaves w, its norm parts and H alone for
-// every RHS whose first pass kept ||w|| >= eta ||A v_j|| (with A v_j =
-// sum_i H[i][j] V_i + w: ||w||^2 >= eta^2 / (1 - eta^2) sum_i |H[i][j]|^2),
-// the criterion of Kahan and Parlett: after one projection the part of w
-// left in the basis's span is of the order of the rounding unit times
-// ||A v_j||, at most 1/eta times the rounding unit relative to ||w||.
-constexpr double kCgs2Eta = 0.1;
+// nsub = 4.  skip (nullable; a second pass, mode 1): the pass leaves w, its
+// norm parts and H alone for every RHS with skip[b] != 0 (finish_norm_kernel).
 template <int NV, typename VB, typename WB>
 __global__ void __launch_bounds__(256, NV == 20 ? 4 : 1)
 gs_update_el_kernel(const VB* __restrict__ V, WB* __restrict__ w, const RhsVec* __restrict__ rv,
@@ -664,7 +682,7 @@ gs_update_el_kernel(const VB* __restrict__ V, WB* __restrict__ w, const RhsVec* 
                     int nvec, int64_t ut, int do_norm, double* __restrict__ npart, int maxB,
                     double2* __restrict__ H, int m, int j, int mode, const int* __restrict__ run_prev,
                     const int* __restrict__ idle, int part_chunk, double2* __restrict__ partial2, int maxP2,
-                    const int* __restrict__ rl, int B, int64_t nb_max, const double* __restrict__ skip_nsum) {
+                    const int* __restrict__ rl, int B, int64_t nb_max, const double* __restrict__ skip) {
   if (run_prev && *run_prev == 0) return;
   constexpr bool FOLD = NV > 0;
   constexpr int kEl = 256;  // elements per block: four 64-element runs
@@ -681,14 +699,7 @@ gs_update_el_kernel(const VB* __restrict__ V, WB* __restrict__ w, const RhsVec* 
     const RhsVec r = rv[b];
     const int64_t nb = (r.N + kEl - 1) / kEl;
     if (blk >= nb) continue;
-    if (skip_nsum) {  // the same decision in every block of the RHS
-      double hh = 0.0;
-      for (int i = 0; i < nvec; ++i) {
-        const double2 h = H[(size_t)b * (m + 1) * m + (size_t)i * m + j];
-        hh += h.x * h.x + h.y * h.y;
-      }
-      if (skip_nsum[b] >= kCgs2Eta * kCgs2Eta / (1.0 - kCgs2Eta * kCgs2Eta) * hh) continue;  // uniform
-    }
+    if (skip && skip[b] != 0.0) continue;
     const int P = n_part > 0 ? n_part : (int)((r.N + part_chunk - 1) / part_chunk);
     // this item's element of w and of the basis (the first 8 vectors without
     // folding) are loaded before the coefficient sums, which do not need them
@@ -780,7 +791,7 @@ gs_update_el_kernel(const VB* __restrict__ V, WB* __restrict__ w, const RhsVec* 
 }
 
 // The second Gram-Schmidt pass of the folded updates is selective (see
-// gs_update_el_kernel's skip_nsum) unless R3M_CGS2_FULL=1 asks for it at
+// finish_norm_kernel) unless R3M_CGS2_FULL=1 asks for it at
 // every step.
 bool selective_cgs2() {
   static const bool sel = [] {
@@ -1700,14 +1711,14 @@ struct GmresRun {
     if (nvec <= fold_max_vec(maxN, sizeof(VB) == sizeof(float2)) && W.dpart2) {
       // the first update also forms the second pass's inner products; on
       // long vectors it also takes ||w||^2, and the second pass runs only
-      // where the first lost more than half of the squared norm (the first
-      // pass's norm parts then stand for the RHS that skip it)
+      // where the first does not suffice (the first pass's norm parts then
+      // stand for the RHS that skip it)
       const int maxP2 = (int)fold_blocks(maxN, sizeof(VB) == sizeof(float2));
       const bool sel = long_vec && nsub == 4 && selective_cgs2();
       update(nvec <= 8 ? 2 : 4, h0, h0P, h0n, sel ? 1 : 0, 0, kDotChunk, W.dpart2, maxP2, nullptr);
       if (sel)
         hipLaunchKernelGGL(finish_norm_kernel, dim3(B), dim3(256), 0, s, (const double*)W.npart, maxB, W.rv, W.nsum,
-                           live, W.idle, nsub);
+                           live, W.idle, nsub, (const double2*)W.H, m, j, nvec);
       const bool fin2 = long_vec || maxP2 > kPartials2InUpdate;
       if (fin2)
         hipLaunchKernelGGL(finish_partials_kernel, dim3((nvec + 3) / 4, B), dim3(256), 0, s, (const double2*)W.dpart2,
@@ -1725,7 +1736,7 @@ struct GmresRun {
     }
     if (long_vec)
       hipLaunchKernelGGL(finish_norm_kernel, dim3(B), dim3(256), 0, s, (const double*)W.npart, maxB, W.rv, W.nsum,
-                         live, W.idle, nsub);
+                         live, W.idle, nsub, (const double2*)nullptr, 0, 0, 0);
     const double* np = long_vec ? W.nsum : W.npart;
     const int npB = long_vec ? 1 : maxB, npE = long_vec ? 0 : 64 * nsub;
     // blocks of whole units (the preconditioner multiplies per unit)
