@@ -1257,9 +1257,15 @@ constexpr int kSYB = 16 * 64 + 16;                       // bytes of a right-han
 static_assert(2 * kPB * kSYB <= kStage, "the output tile fits a stage");
 // 16 bytes a lane from base + off (off by lane) to LDS bytes lds + 16 lane.  No
 // register is written; wait_loads of the same wave and a barrier make the bytes
-// visible.
+// visible.  The load takes its LDS address from m0, which the compiler holds
+// for itself (it is put back), and the compiler keeps no wait states for what
+// stands inside: five lie between a base that a vector instruction has just
+// written and the load.
 __device__ __forceinline__ void load_to_lds(const void* base, uint32_t off, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds)
+  uint32_t keep;
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\ts_nop 2\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b32 m0, %0"
+               : "=&s"(keep)
+               : "v"(off), "s"(base), "s"(lds)
                : "memory");
 }
 template <int N>
