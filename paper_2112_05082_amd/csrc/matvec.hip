@@ -1581,6 +1581,21 @@ static bool near_on_mfma(const r3m_store* Z) {
   return near_count(Z) <= 128 && ((size_t)2 * n_a + kNearCols) * (2 * n_a + 1) * es <= 96 * 1024;
 }
 
+// row-slab height of near_kernel: the whole state of 40 for complex64, half of
+// it for complex128
+template <typename S>
+constexpr int slab_rows() {
+  return sizeof(S) == 4 ? 40 : 20;
+}
+template <typename S>
+static size_t slab_lds(const r3m_store* Z) {
+  return ((size_t)slab_rows<S>() * (Z->n + 2) + 2 * (size_t)kBU * (Z->n / Z->n_states)) * 2 * sizeof(S);
+}
+template <typename S>
+static bool slab_takes(const r3m_store* Z) {
+  return Z->n / Z->n_states % slab_rows<S>() == 0 && slab_lds<S>(Z) <= 160 * 1024;
+}
+
 // All-dense stores on the one-launch direct product: few unit pairs, or small
 // arrays where the slab kernel would take over from the matrix-core lists.
 // The lines from whole products (us, lists or slab / direct; complex128,
@@ -1588,13 +1603,15 @@ static bool near_on_mfma(const r3m_store* Z) {
 // / 13.3; 4x4 x 128 (33k pairs) 80 / 54, 55 / 51; 6x6 x 32 (41k) 95 / 88, 51 /
 // 62.  Against the slab kernel 10x10 106 / 33, 49 / 20; 12x12 x 24 (498k) 2,605
 // / 1,450, 1,182 / 731; 14x14 x 4 (154k) 528 / 461, 226 / 237; 20x20 (160k) 454
-// / 475, 214 / 238.
+// / 475, 214 / 238.  All with 40 bases a state.  States of 64, whose rows the
+// slab kernel does not cut, take it at every size that the lists do not.
 constexpr int64_t kDirectPairsLists = (int64_t)1 << 15, kDirectPairsSlab = (int64_t)1 << 17;
 constexpr int64_t kDirectUnits = 144;
 static bool dense_direct(const r3m_store* Z, const BatchDesc& bd) {
   if (store_is_spectral(Z) || store_has_far(Z)) return false;
   const bool lists = near_on_mfma(Z);
   if (!lists && bd.max_units <= kDirectUnits) return true;
+  if (!lists && !(Z->near_dtype == R3M_C128 ? slab_takes<double>(Z) : slab_takes<float>(Z))) return true;
   const int64_t most = lists ? kDirectPairsLists : kDirectPairsSlab;
   int64_t pairs = 0;
   for (int64_t u : bd.n_units) {
@@ -1783,6 +1800,8 @@ static void launch_direct(const r3m_store* Z, const BatchDesc& bd, const uint8_t
                           hipStream_t stream, const int* live, const int* idle, int* bad) {
   const int n_a = Z->n / Z->n_states;
   auto kern = n_a == 40 ? dense_direct_kernel<S, XI, YO, 40> : dense_direct_kernel<S, XI, YO, 64>;
+  R3M_REQUIRE(bd.max_units * (n_a / 8) <= max_workgroups(64 * kDirectWaves), R3M_ERR_UNSUPPORTED,
+              "array too large for the dense product");
   hipLaunchKernelGGL(kern, dim3((unsigned)(bd.max_units * (n_a / 8)), bd.B), dim3(64 * kDirectWaves), 0, stream,
                      bd.rhs, states, (const S*)Z->near, Z->Dx, Z->Dy, Z->n, Z->n_states, x, y, live, idle, bad);
   R3M_CHECK_HIP(hipGetLastError());
@@ -1876,12 +1895,10 @@ static void launch_core(const r3m_store* Z, const BatchDesc& bd, const uint8_t* 
     }
   } else {
     const int nwg_near = (bd.n_tiles * hg + kXcd - 1) / kXcd * kXcd;
-    // row-slab height: the whole state for complex64, half of it for complex128
-    constexpr int sr = sizeof(S) == 4 ? 40 : 20;
-    const size_t lds_near = ((size_t)sr * (Z->n + 2) + 2 * (size_t)kBU * n_a) * 2 * sizeof(S);
-    R3M_REQUIRE(n_a % sr == 0 && lds_near <= 160 * 1024, R3M_ERR_UNSUPPORTED, "near row slab does not fit in LDS");
-    hipLaunchKernelGGL((near_kernel<S, sr>), dim3(nwg_near), dim3(256), lds_near, stream, bd.rhs, bd.tiles, states,
-                       (const S*)Z->near, Nx, Ny, Z->n, n_a, Z->n_states, xs, (S*)part, tu, groups, hg, bd.n_tiles);
+    R3M_REQUIRE(slab_takes<S>(Z), R3M_ERR_UNSUPPORTED, "near row slab does not fit in LDS");
+    hipLaunchKernelGGL((near_kernel<S, slab_rows<S>()>), dim3(nwg_near), dim3(256), slab_lds<S>(Z), stream, bd.rhs,
+                       bd.tiles, states, (const S*)Z->near, Nx, Ny, Z->n, n_a, Z->n_states, xs, (S*)part, tu, groups,
+                       hg, bd.n_tiles);
   }
   R3M_CHECK_HIP(hipGetLastError());
   hipLaunchKernelGGL((reduce_groups_kernel<S, XT>), dim3(ceil_div((size_t)bd.max_units * n_a, 64), bd.B),
