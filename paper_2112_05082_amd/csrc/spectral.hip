@@ -296,7 +296,7 @@ __global__ void __launch_bounds__(256) fft_kernel(FftArgs<T> A) {
   int64_t g0;  // grid of line 0; line li lies in grid g0 + li (chan) or g0
   int lig0;    // its line within the grid; line li is lig0 (chan) or lig0 + li
   if (chan) {
-    const int ncg = A.n >> A.lg_lpw;
+    const int ncg = (A.n + lpw - 1) >> A.lg_lpw;
     const int64_t id = blockIdx.x;
     const int cg = (int)(id % ncg);
     const int64_t rest = id / ncg;
@@ -393,7 +393,7 @@ __global__ void __launch_bounds__(256) fft_kernel(FftArgs<T> A) {
           a[it][r] = {0, 0};
           if constexpr (MODE == kEmbedRows) {
             const int dx = gx <= A.Dx ? gx : gx - G, dy = gy <= A.Dy ? gy : gy - Gy;
-            if (in && dx >= -A.Dx) {
+            if (in && dx >= -A.Dx && g0 + li[it] < A.n) {
               const double2 z = A.dense[((int64_t)(dy + A.Dy) * (2 * A.Dx + 1) + (dx + A.Dx)) * A.n + g0 + li[it]];
               a[it][r] = {(T)z.x, (T)z.y};
             }
@@ -407,6 +407,7 @@ __global__ void __launch_bounds__(256) fft_kernel(FftArgs<T> A) {
   };
   const T scale = T(1) / (T)((int64_t)1 << lgG2);
   auto store = [&](const C2<T>& v, int li, int e) {
+    if (MODE == kEmbedRows && g0 + li >= A.n) return;  // the last workgroup of a row may have lines to spare
     int gx, gy;
     at_line(li, e, gx, gy);
     if (MODE == kInvRows) {
@@ -453,7 +454,11 @@ int fft_lpw_log(int lgG, int lg_lpg) {
 
 // one pass over every row or column (by MODE) of n_grids Gy x Gx grids; the
 // compacting row passes group lpw channels of one RHS instead (lpw the
-// largest power of two dividing n that fits)
+// largest power of two dividing n that fits), the embedding the same row of
+// lpw adjacent grids (all that fit: with odd n, powers of two that divide n^2
+// leave one line to a workgroup; us for n = 41, half-extent 31: 97 before the
+// embedding read the blocks itself, 639 with such groups, 50 now; n = 83, 63:
+// 1,917, 7,097, 886)
 template <typename T, int MODE, typename VT>
 void fft_pass(FftArgs<T> A, int lgGx, int lgGy, int64_t n_grids, hipStream_t s) {
   constexpr bool rows = MODE == kFwdRows || MODE == kInvRows || MODE == kEmbedRows;
@@ -464,9 +469,9 @@ void fft_pass(FftArgs<T> A, int lgGx, int lgGy, int64_t n_grids, hipStream_t s) 
   if (chan) {
     constexpr int LKE = fft_ke<T>() == 16 ? 4 : 3;
     int lg = 0;
-    while (lg < 8 + LKE - A.lgG && (A.n & ((2 << lg) - 1)) == 0) ++lg;
-    A.lg_lpw = std::max(0, lg);
-    n_wg = (n_grids >> A.lg_lpw) << A.lg_lpg;
+    while (lg < 8 + LKE - A.lgG && (MODE == kEmbedRows ? A.n >> lg > 1 : (A.n & ((2 << lg) - 1)) == 0)) ++lg;
+    A.lg_lpw = lg;
+    n_wg = (n_grids / A.n * ((A.n + (1 << lg) - 1) >> lg)) << A.lg_lpg;
   } else {
     A.lg_lpw = fft_lpw_log<T>(A.lgG, A.lg_lpg);
     n_wg = (n_grids << A.lg_lpg) >> A.lg_lpw;
