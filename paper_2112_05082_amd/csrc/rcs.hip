@@ -321,7 +321,8 @@ rcs_kernel(GeomDev g, const RhsDev* __restrict__ rhs, const uint8_t* __restrict_
   const int chunk = (int)(grp / B), b = (int)(grp % B), dgrp = (int)(slot % n_dgrp);
   const RhsDev R = rhs[b];
   const int64_t units = (int64_t)R.Lx * R.Ly;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 15, kq = lane >> 4;
+  const int lane = threadIdx.x & 63, col = lane & 15, kq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int2* list = list_s[wave];
   int d[kRcsDirTiles];
   double kx[kRcsDirTiles], ky[kRcsDirTiles];  // phase per metre along x and y
@@ -339,7 +340,14 @@ rcs_kernel(GeomDev g, const RhsDev* __restrict__ rhs, const uint8_t* __restrict_
   const int sb = (n_a + kRcsRows - 1) / kRcsRows, cb = (n_v - n_a + kRcsRows - 1) / kRcsRows;
   const int n_pass = n_states * sb + cb;
   const int64_t c_lo = (int64_t)chunk * chunk_units, c_hi = min(units, c_lo + chunk_units);
-  for (int pass = 0; pass < n_pass; ++pass) {
+  // units of one list would keep one wave busy and leave the others their
+  // passes' ends: the waves take the passes in turn instead (us a call, units
+  // split / passes in turn: 6x6 with four states 136 / 85, 12x12 154 / 94, 16
+  // states of one basis 214 / 99, 12x12 of two states x 64 right-hand sides x
+  // 360 directions 183 / 136)
+  const bool by_pass = c_hi - c_lo <= kRcsList;
+  const int64_t u_lo = c_lo + (by_pass ? 0 : wave * kRcsList);
+  for (int pass = by_pass ? wave : 0; pass < n_pass; pass += by_pass ? kRcsWaves : 1) {
     const bool shared = !FULL && pass >= n_states * sb;
     const int s = shared ? -1 : pass / sb;
     const int r0 = shared ? n_a + (pass - n_states * sb) * kRcsRows : (pass % sb) * kRcsRows;
@@ -349,7 +357,7 @@ rcs_kernel(GeomDev g, const RhsDev* __restrict__ rhs, const uint8_t* __restrict_
     for (int t = 0; t < kRcsRowTiles; ++t)
 #pragma unroll
       for (int e = 0; e < kRcsDirTiles; ++e) ac[t][e] = as[t][e] = f64x4{0, 0, 0, 0};
-    for (int64_t u0 = c_lo + wave * kRcsList; u0 < c_hi; u0 += kRcsUnits) {
+    for (int64_t u0 = u_lo; u0 < c_hi; u0 += kRcsUnits) {
       // the state's units among the next 256, in order
       int cnt = 0;
       __builtin_amdgcn_wave_barrier();
