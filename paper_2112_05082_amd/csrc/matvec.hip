@@ -1538,8 +1538,12 @@ static bool store_has_far(const r3m_store* Z) { return Z->near_radius < std::max
 // 32x32: 48 groups, 768 workgroups, 123 us; 64 groups, 1,024 workgroups, the
 // former default, 145; 96 groups 127); where the arrays differ the rounds
 // blur, and smaller workgroups shorten the end (20x20 to 32x32 x 12: 7 groups
-// 1,038 us, 16 793, 28 794).
+// 1,038 us, 16 793, 28 794).  Every group's partial sums are written and read
+// again, kFarReduce displacements' time a megabyte, which small equal arrays
+// notice (1-bit 8x8 x 6: 64 groups 37.2 us, 80 37.6, 128 40.9, 6x6 x 8: 33.2,
+// 34.7, 38.0).
 constexpr int kFarStart = 3;
+constexpr double kFarReduce = 0.4;
 static int default_groups(const r3m_store* Z, const BatchDesc& bd) {
   if (!store_has_far(Z) || bd.n_tiles == 0) return choose_chunks(bd, 64);
   const double slots = 256.0 * (Z->near_dtype == R3M_C64 && Z->n / Z->n_states == 40 ? R3M_FAR_WAVES_PER_EU_F32
@@ -1553,11 +1557,14 @@ static int default_groups(const r3m_store* Z, const BatchDesc& bd) {
     most = std::max(most, nd);
     equal = equal && bd.Lx[b] == bd.Lx[0] && bd.Ly[b] == bd.Ly[0];
   }
+  // megabytes of a group's partial sums
+  const double part = (double)bd.total_units * (Z->n / Z->n_states) * (Z->near_dtype == R3M_C128 ? 16e-6 : 8e-6);
   int best = 1;
   double best_t = 1e300;
-  for (int g = 1; g <= max_groups(bd); ++g) {
+  for (int g = 1, most_g = max_groups(bd); g <= most_g; ++g) {
     const double wgs = (double)bd.n_tiles * g, one = most / g + kFarStart;
-    const double t = equal ? std::ceil(wgs / slots) * one : (work + wgs * kFarStart) / slots + 0.5 * one;
+    const double t = equal ? std::ceil(wgs / slots) * one + kFarReduce * part * g
+                           : (work + wgs * kFarStart) / slots + 0.5 * one;
     if (t < best_t) {
       best_t = t;
       best = g;
