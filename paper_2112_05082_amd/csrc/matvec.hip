@@ -1605,27 +1605,60 @@ static bool slab_takes(const r3m_store* Z) {
 
 // All-dense stores on the one-launch direct product: few unit pairs, or small
 // arrays where the slab kernel would take over from the matrix-core lists.
-// The lines from whole products (us, lists or slab / direct; complex128,
-// complex64): against the lists (up to 6x6 units) 6x6 alone 36.5 / 13.2, 30.4
-// / 13.3; 4x4 x 128 (33k pairs) 80 / 54, 55 / 51; 6x6 x 32 (41k) 95 / 88, 51 /
-// 62.  Against the slab kernel 10x10 106 / 33, 49 / 20; 12x12 x 24 (498k) 2,605
-// / 1,450, 1,182 / 731; 14x14 x 4 (154k) 528 / 461, 226 / 237; 20x20 (160k) 454
-// / 475, 214 / 238.  All with 40 bases a state.  States of 64, whose rows the
-// slab kernel does not cut, take it at every size that the lists do not.
-constexpr int64_t kDirectPairsLists = (int64_t)1 << 15, kDirectPairsSlab = (int64_t)1 << 17;
+// Both lines are from whole products of 40 bases a state (us, lists or slab /
+// direct).  States of 64, whose rows the slab kernel does not cut, take the
+// direct product at every size that the lists do not.
+//
+// Against the lists (up to 6x6 units), complex128 and complex64; two states:
+// 6x6 alone 36.5 / 13.2, 30.4 / 13.3, x 21 (27k pairs) 65 / 59, 45 / 42, x 25
+// (32k) 73 / 70, 47 / 50; 5x5 x 52 (33k) 74 / 57, 49 / 50; 4x4 x 127 (33k) 81 /
+// 50, 56 / 50; 2x2 x 2000 (32k) 258 / 109, 239 / 68; four states: 6x6 x 20 (26k)
+// 94 / 82, 52 / 48, x 25 102 / 101, 55 / 57; 5x5 x 52 87 / 94, 51 / 52; 4x4 x 127
+// 84 / 67, 50 / 53.  Past 33k pairs 4x4 x 128 80 / 54, 55 / 51; 6x6 x 32 (41k) 95
+// / 88, 51 / 62.
+constexpr int64_t kDirectPairsLists = (int64_t)1 << 15, kDirectPairsLate = 28672;
+static bool direct_beats_lists(const r3m_store* Z, const BatchDesc& bd, int64_t pairs) {
+  // complex64 or more than two states: the lists are ahead a little earlier on
+  // arrays of 5x5 (both: 4x4) units and more
+  const bool c64 = Z->near_dtype == R3M_C64, states = Z->n_states > 2;
+  const bool late = (c64 || states) && bd.max_units >= (c64 && states ? 16 : 25);
+  return pairs <= (late ? kDirectPairsLate : kDirectPairsLists);
+}
+// Against the slab kernel.  Complex128, two states: 10x10 106 / 33; 12x12 x 24
+// (498k) 2,605 / 1,450; 14x14 x 3 (115k) 405 / 346, x 4 528 / 461; 20x20 (160k)
+// 454 / 475; complex64, four states: 8x8 x 600 11,200 / 4,030, 19x19 608 / 262.
+// Complex64 with one or two states a unit is where the slab kernel is near: it
+// takes 8x8 tiles of units with every displacement between a tile and an
+// array, and the line is how many unit pairs these cover for each real one (r).
+// Two states: 14x14 (r 2.9; 38k pairs) 77 / 63, x 3 (115k) 176 / 180; 15x15 (2.5)
+// 76 / 86, x 2 133 / 153; 18x18 (3.4; 105k) 167 / 171; 13x13 x 4 (3.6; 114k) 239 /
+// 179; 17x17 (4.0; 84k) 162 / 130; 8x8 (3.5) x 32 (131k) 199 / 184, x 128 713 /
+// 727, x 600 3,146 / 3,391; 12x12 (4.5) x 100 3,717 / 3,071; 7x7 (5.2) x 600 2,083
+// / 1,998.  One state: 13x13 (29k) 59 / 51, x 4 188 / 169; 14x14 53 / 59; 15x15 59 /
+// 83; 18x18 127 / 163; 8x8 x 32 147 / 183, x 600 2,143 / 3,383; 7x7 x 32 (77k) 121 /
+// 110, x 128 355 / 429; 12x12 x 100 2,668 / 2,852; 11x11 (5.7) x 64 1,396 / 1,300.
+constexpr int64_t kDirectPairsSlab = (int64_t)1 << 17;
 constexpr int64_t kDirectUnits = 144;
+static bool direct_beats_slab(const r3m_store* Z, const BatchDesc& bd, int64_t pairs) {
+  const bool small = bd.max_units <= kDirectUnits;
+  if (Z->near_dtype == R3M_C128 || Z->n_states > 2) return small || pairs <= kDirectPairsSlab;
+  const bool one = Z->n_states == 1;
+  if (pairs <= (one ? 28672 : 40960)) return true;
+  int64_t cover = 0;
+  for (int b = 0; b < bd.B; ++b)
+    cover += (int64_t)((bd.Lx[b] + kBW - 1) / kBW) * ((bd.Ly[b] + kBH - 1) / kBH) * (bd.Lx[b] + kBW - 1) *
+             (bd.Ly[b] + kBH - 1) * kBU;
+  const double r = (double)cover / (double)pairs;
+  if (pairs <= kDirectPairsSlab) return r >= 3.55 || (small && !one);
+  return small && r >= (one ? 5.6 : 3.55);
+}
 static bool dense_direct(const r3m_store* Z, const BatchDesc& bd) {
   if (store_is_spectral(Z) || store_has_far(Z)) return false;
   const bool lists = near_on_mfma(Z);
-  if (!lists && bd.max_units <= kDirectUnits) return true;
   if (!lists && !(Z->near_dtype == R3M_C128 ? slab_takes<double>(Z) : slab_takes<float>(Z))) return true;
-  const int64_t most = lists ? kDirectPairsLists : kDirectPairsSlab;
   int64_t pairs = 0;
-  for (int64_t u : bd.n_units) {
-    pairs += u * u;
-    if (pairs > most) return false;
-  }
-  return true;
+  for (int64_t u : bd.n_units) pairs += u * u;
+  return lists ? direct_beats_lists(Z, bd, pairs) : direct_beats_slab(Z, bd, pairs);
 }
 
 // near partial slots: one per displacement on the matrix-core path; otherwise

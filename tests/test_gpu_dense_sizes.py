@@ -11,10 +11,14 @@ pytestmark = pytest.mark.gpu
 
 
 # 64 bases: 169 units alone, 153,664 pairs, arrays of one row; 40 bases: the
-# lists from 32,768 pairs, the slab kernel from 131,072
+# lists from 28,672 or 32,768 pairs, the slab kernel from 28,672, 40,960 or
+# 131,072 (by type, states and how well its 8x8 tiles fit the array)
 @pytest.mark.parametrize("n_a,S,D,shapes", [
     (64, 1, 12, [(13, 13)]), (64, 2, 13, [(14, 14)] * 4), (64, 2, 19, [(20, 8), (1, 20), (13, 13)]),
-    (64, 2, 5, [(6, 6)] * 26), (40, 2, 5, [(6, 6)] * 26), (40, 1, 13, [(14, 14)] * 4)])
+    (64, 2, 5, [(6, 6)] * 26), (40, 2, 5, [(6, 6)] * 26), (40, 1, 13, [(14, 14)] * 4),
+    (40, 2, 5, [(6, 6)] * 23), (40, 4, 4, [(5, 5)] * 48), (40, 4, 3, [(4, 4)] * 120), (40, 2, 3, [(4, 4)] * 120),
+    (40, 1, 13, [(14, 14)]), (40, 2, 14, [(15, 15)]), (40, 2, 7, [(8, 8)] * 33), (40, 1, 7, [(7, 7)] * 56),
+    (40, 2, 23, [(24, 2), (15, 15)])])
 @pytest.mark.parametrize("store,vec", [("c128", "c128"), ("c64", "c128"), ("c64", "c64")])
 def test_dense_product(n_a, S, D, shapes, store, vec):
     from paper_2112_05082_amd import r3m
