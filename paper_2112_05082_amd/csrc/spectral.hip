@@ -1260,17 +1260,31 @@ constexpr int kSR = 64;                                  // right-hand sides of 
 constexpr int kStZ = 4 * kPM * 64, kStage = kStZ + 4 * kSR * 64, kStages = 4;
 constexpr int kSYB = 16 * 64 + 16;                       // bytes of a right-hand side's output rows, padded
 static_assert(2 * kPB * kSYB <= kStage, "the output tile fits a stage");
-// 16 bytes a lane from base + off (off by lane) to LDS bytes lds + 16 lane.  No
-// register is written; wait_loads of the same wave and a barrier make the bytes
-// visible.  The load takes its LDS address from m0, which the compiler holds
-// for itself (it is put back), and the compiler keeps no wait states for what
-// stands inside: five lie between a base that a vector instruction has just
-// written and the load.
-__device__ __forceinline__ void load_to_lds(const void* base, uint32_t off, uint32_t lds) {
+// 16 bytes a lane from b[i] + off (off by lane) to LDS bytes lds + i step + 16
+// lane, i < 4.  No register is written; wait_loads of the same wave and a
+// barrier make the bytes visible.  The loads take their LDS address from m0,
+// which the compiler holds for itself (it is put back), and the compiler keeps
+// no wait states for what stands inside: five lie between a base that a vector
+// instruction has just written and the first load, one between m0 and a load.
+__device__ __forceinline__ void load4_to_lds(const void* b0, const void* b1, const void* b2, const void* b3, uint32_t off,
+                                             uint32_t lds, uint32_t step) {
+  uint32_t keep;
+  asm volatile(
+      "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %6\n\ts_nop 2\n\tglobal_load_lds_dwordx4 %1, %2\n\t"
+      "s_mov_b32 m0, %7\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\t"
+      "s_mov_b32 m0, %8\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %4\n\t"
+      "s_mov_b32 m0, %9\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %5\n\t"
+      "s_mov_b32 m0, %0"
+      : "=&s"(keep)
+      : "v"(off), "s"(b0), "s"(b1), "s"(b2), "s"(b3), "s"(lds), "s"(lds + step), "s"(lds + 2 * step),
+        "s"(lds + 3 * step)
+      : "memory");
+}
+__device__ __forceinline__ void load_to_lds(const void* b, uint32_t off, uint32_t lds) {
   uint32_t keep;
   asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\ts_nop 2\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b32 m0, %0"
                : "=&s"(keep)
-               : "v"(off), "s"(base), "s"(lds)
+               : "v"(off), "s"(b), "s"(lds)
                : "memory");
 }
 template <int N>
@@ -1348,8 +1362,8 @@ spec_product_stream_kernel(const C2<float>* __restrict__ Zh, const C2<float>* __
     if (!more) return;
     const uint32_t dst = lds0 + l_stage * kStage + (w < 4 ? w * (kPM * 64) : kStZ + p * 1024);
     const uint32_t dst_step = w < 4 ? 1024 : kSR * 64;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) load_to_lds(l_base + min(i, l_last) * l_step, l_off, dst + i * dst_step);
+    load4_to_lds(l_base, l_base + min(1, l_last) * l_step, l_base + min(2, l_last) * l_step,
+                 l_base + min(3, l_last) * l_step, l_off, dst, dst_step);
     if (w < 4) load_to_lds(l_base + l_last * l_step, l_off, dst + 4 * dst_step);
     l_base += 4 * K * 8;
     l_stage = (l_stage + 1) & 3;
