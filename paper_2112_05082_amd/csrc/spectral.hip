@@ -1536,14 +1536,28 @@ void launch_product_mfma(const C2<T>* Zh, const C2<T>* X, C2<T>* Y, int n, int64
 }
 
 constexpr int kStreamWgs = 256;  // one per CU
-// wide batches on stores whose rows fill 16-row tiles; the lanes' offsets in
+// Wide batches on stores whose rows fill 16-row tiles; the lanes' offsets in
 // the grids of 16 rows or right-hand sides take 31 bits.  Below four RHS tiles
-// (1-bit 32x32, 64 right-hand sides: 164 us against 172) the workgroup's last
-// tiles would be empty.
+// the workgroup's last tiles would be empty.  The other kernel's workgroups
+// hold half the right-hand sides and fit a CU in pairs, so it is ahead where
+// the items (frequency tiles x row groups x groups of four RHS tiles) leave
+// half of the CUs idle or start a second round that they do not fill, and on
+// five or six RHS tiles, whose second group is nearly empty, once there are
+// more than two rounds.  us, {2,4,2} / streamed: 1-bit, 128 items (4x4, 1,024
+// right-hand sides; 8x8, 256; 16x16, 64) 51 / 67, 50 / 66, 51 / 67; 160 (8x8,
+// 320) 73 / 69; 256 (16x16, 65 and 128) 73 / 69, 81 / 76; 320 and 384 (8x8, 640
+// and 768) 116 / 130, 118 / 133; 384 (16x16, 160) 121 / 124; 512 (8x8, 1,024;
+// 16x16, 256; 32x32, 64) 166 / 151, 172 / 146, 185 / 168; 2-bit 16x16, 64 (256)
+// 154 / 129, 65 (512) 246 / 229; five tiles: 1-bit 32x32 (1,024) 235 / 258, 64x64
+// (4,096) 834 / 1,145, 2-bit 32x32 (2,048) 767 / 902; nine: 406 / 341, 1,383 /
+// 1,228, 1,328 / 1,096.
 bool product_streams(int n, int64_t G2, int B, bool tr) {
-  const int64_t n_bt = (B + kPB - 1) / kPB;
-  return !tr && n % 16 == 0 && G2 >= 16 && n_bt >= 4 && (int64_t)16 * n * G2 * 8 < ((int64_t)1 << 31) &&
-         G2 / 8 * ((n + kPM - 1) / kPM) * ((n_bt + 3) / 4) < ((int64_t)1 << 31) - 8 * kStreamWgs;
+  const int64_t n_bt = (B + kPB - 1) / kPB, items = G2 / 8 * ((n + kPM - 1) / kPM) * ((n_bt + 3) / 4);
+  if (tr || n % 16 != 0 || G2 < 16 || n_bt < 4 || (int64_t)16 * n * G2 * 8 >= ((int64_t)1 << 31) ||
+      items >= ((int64_t)1 << 31) - 8 * kStreamWgs)
+    return false;
+  if (items <= kStreamWgs / 2 || (items > kStreamWgs && items <= kStreamWgs * 3 / 2)) return false;
+  return !((n_bt == 5 || n_bt == 6) && items > 2 * kStreamWgs);
 }
 // tl: room for the live-tile list (ceil(B / 16) + 1 ints), used with idle flags
 void launch_product_stream(const C2<float>* Zh, const C2<float>* X, C2<float>* Y, int n, int64_t G2, int B,
