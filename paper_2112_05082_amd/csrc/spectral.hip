@@ -1623,15 +1623,20 @@ void product(const C2<T>* Zh, const C2<T>* X, C2<T>* Y, int n, int64_t G2, int B
     if (B <= 4) R3M_VECTOR(4, 4);
     R3M_VECTOR(4, 8);
   } else {
-    // two RHS tiles per workgroup where there are two, as in complex64, in the
-    // contiguous order below 32 tiles (ms, contiguous / RHS tile first: 1-bit
-    // 64x64, 128 right-hand sides 2.39 / 4.41, 256 4.52 / 4.69, 512 9.25 / 9.43,
-    // 1024 20.97 / 17.79; 2-bit 32x32, 256 3.92 / 3.96, 512 8.79 / 7.63); one tile against two, us: 1-bit 48x48, 24 right-hand sides 788 /
-    // 648, 48 1226 / 1151, 2-bit 32x32 716 / 580, 1089 / 1000, 1-bit 64x64, 1536
-    // 35,170 / 27,410.  (Kept to two waves per SIMD, 158 registers instead of
-    // 144, one tile is faster too: 1-bit 48x48, 4
-    // right-hand sides 416 / 391, 2-bit 32x32, 16 492 / 468.)
-    if (B > kPB)
+    // two RHS tiles per workgroup where there are two and three quarters of the
+    // CUs have one, as in complex64, in the contiguous order below 32 tiles (ms,
+    // contiguous / RHS tile first: 1-bit 64x64, 128 right-hand sides 2.39 / 4.41,
+    // 256 4.52 / 4.69, 512 9.25 / 9.43, 1024 20.97 / 17.79; 2-bit 32x32, 256 3.92
+    // / 3.96, 512 8.79 / 7.63); one tile against two, us: 1-bit 48x48, 24
+    // right-hand sides 788 / 648, 48 1226 / 1151, 2-bit 32x32 716 / 580, 1089 /
+    // 1000, 1-bit 64x64, 1536 35,170 / 27,410; whole products on small grids,
+    // 1-bit 3x3 x 20 (16 workgroups of two tiles) 45 / 57, 6x6 x 32 (64) 58 / 73, x
+    // 64 (128) 72 / 86, 2-bit 6x6 x 32 (128) 88 / 114, 3x3 x 129 (160) 127 / 131.
+    // (Kept to two waves per SIMD, 158 registers instead of 144, one tile is
+    // faster too: 1-bit 48x48, 4 right-hand sides 416 / 391, 2-bit 32x32, 16 492 /
+    // 468.)
+    const int64_t wg2t = (G2 + 3) / 4 * ((n + kPM - 1) / kPM) * (((B + kPB - 1) / kPB + 1) / 2);
+    if (B > kPB && wg2t >= 192)
       return launch_product_mfma<T, 1, 4, 2>(Zh, X, Y, n, G2, B, tr, lgGx, lgGy, s, live, idle, tl, std::max(rf, 32),
                                              lkg);
     if (B > kSpecNarrow64) R3M_MATRIX(1, 4, 1);
