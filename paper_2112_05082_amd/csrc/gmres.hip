@@ -40,9 +40,9 @@ constexpr int kFoldMaxVecEl = 32;
 // update's blocks (two loads); above, a launch of its own sums them once.
 constexpr int kPartialsInUpdate = 64;
 constexpr int kPartials2InUpdate = 128;
-// longest vector of the batch from which the updates run element-parallel,
-// by basis type (see update_runs)
-constexpr int64_t kElementMin32 = 8192, kElementMin64 = 16384;
+// vector length from which the updates run element-parallel, by basis type
+// (see element_line)
+constexpr int64_t kElementMin32 = 2560, kElementMin64 = 8192;
 constexpr int kCheckEvery = 4;
 
 struct RhsVec {
@@ -381,14 +381,14 @@ __device__ __forceinline__ void wave_transpose_sum(double2 (&x)[NV], int lane) {
 // (basis entries kept in their stored type).  Each wave sums its lanes'
 // products with wave_transpose_sum, then the block adds the waves in a fixed
 // order.  The blocks stride over the items of the right-hand sides of rl (a
-// live list, see rhs_count), or of all B.  The consumer kernel sums the
-// partials itself (no grid-wide fence here).
+// live list, see rhs_count), or of all B, that have at most `most` unknowns.
+// The consumer kernel sums the partials itself (no grid-wide fence here).
 template <typename VB, typename WB, int DV = dot_vec<VB>()>
 __global__ void __launch_bounds__(kDotThreads)
 dots_partials_kernel(const VB* __restrict__ A, int64_t a_stride, const WB* __restrict__ Bv,
                      const RhsVec* __restrict__ rv, int nvec, int maxP, double2* __restrict__ partial,
                      int* __restrict__ reset, const int* __restrict__ live, const int* __restrict__ idle,
-                     const int* __restrict__ rl, int B) {
+                     const int* __restrict__ rl, int B, int64_t most) {
   constexpr int kDotVec = DV;  // vectors per item (fewer for small bases)
   constexpr int kShV = kDotVec == 1 ? 6 : kDotVec == 2 ? 5 : kDotVec == 4 ? 4 : kDotVec == 8 ? 3 : 2;
   static_assert(kDotVec == 1 || kDotVec == 2 || kDotVec == 4 || kDotVec == 8 || kDotVec == 16, "kDotVec");
@@ -408,7 +408,7 @@ dots_partials_kernel(const VB* __restrict__ A, int64_t a_stride, const WB* __res
     if (!rl && idle && idle[b]) continue;
     const RhsVec r = rv[b];
     const int64_t P = (r.N + kDotChunk - 1) / kDotChunk;
-    if (p >= P) continue;
+    if (p >= P || r.N > most) continue;
     const int i0 = grp * kDotVec;
     const int nv = min(kDotVec, nvec - i0);
     const WB* bb = Bv + r.off;
@@ -462,20 +462,25 @@ dots_partials_kernel(const VB* __restrict__ A, int64_t a_stride, const WB* __res
   }
 }
 
+// elements of an update block of a right-hand side of N unknowns
+__host__ __device__ inline int update_elements(int64_t N, int64_t line) { return N > line ? 256 : 64; }
+
 // Many partials per vector (see kPartialsInUpdate): the partials of
 // dots_partials_kernel (one per part_chunk elements) or of the folded update
-// (one per update block) summed once, in a fixed order, into out[b][i], so
-// that the update kernel's blocks read one value per vector instead of every
-// partial.  Grid (ceil(nvec / 4), B), one wave per vector.
+// (part_chunk 0: one per update block) summed once, in a fixed order, into
+// out[b][i], so that the update kernel's blocks read one value per vector
+// instead of every partial.  Grid (ceil(nvec / 4), B), one wave per vector.
 __global__ void __launch_bounds__(256)
 finish_partials_kernel(const double2* __restrict__ partial, int maxP, int nvec, const RhsVec* __restrict__ rv,
                        double2* __restrict__ out, const int* __restrict__ run_prev, const int* __restrict__ idle,
-                       int part_chunk) {
+                       int part_chunk, int64_t line) {
   if (run_prev && *run_prev == 0) return;
   if (idle && idle[blockIdx.y]) return;
   const int i = blockIdx.x * 4 + (threadIdx.x >> 6), b = blockIdx.y;
   if (i >= nvec) return;
-  const int P = (int)((rv[b].N + part_chunk - 1) / part_chunk);
+  const int64_t N = rv[b].N;
+  const int chunk = part_chunk > 0 ? part_chunk : update_elements(N, line);
+  const int P = (int)((N + chunk - 1) / chunk);
   const double2 t = wave_sum_partials2(partial + ((size_t)b * nvec + i) * maxP, P);
   if ((threadIdx.x & 63) == 0) out[(size_t)b * nvec + i] = t;
 }
@@ -496,13 +501,13 @@ constexpr double kCgs2Eta = 0.1;
 __global__ void __launch_bounds__(256)
 finish_norm_kernel(const double* __restrict__ npart, int maxB, const RhsVec* __restrict__ rv,
                    double* __restrict__ out, const int* __restrict__ run_prev, const int* __restrict__ idle,
-                   int nsub, const double2* __restrict__ H, int m, int j, int nvec) {
+                   const double2* __restrict__ H, int m, int j, int nvec) {
   if (run_prev && *run_prev == 0) return;
   if (idle && idle[blockIdx.x]) return;
   __shared__ double2 sh[4];
   __shared__ double h2[kFoldMaxVecEl];
   const int b = blockIdx.x;
-  const int64_t nb = (rv[b].N + 64 * nsub - 1) / (64 * nsub);  // gs_update_kernel's blocks
+  const int64_t nb = (rv[b].N + 255) / 256;  // gs_update_el_kernel's blocks
   if (H && threadIdx.x < nvec) {
     const double2 h = H[(size_t)b * (m + 1) * m + (size_t)threadIdx.x * m + j];
     h2[threadIdx.x] = h.x * h.x + h.y * h.y;
@@ -520,35 +525,150 @@ finish_norm_kernel(const double* __restrict__ npart, int maxB, const RhsVec* __r
   out[b] = s2.x >= kCgs2Eta * kCgs2Eta / (1.0 - kCgs2Eta * kCgs2Eta) * hh ? 1.0 : 0.0;
 }
 
+// Where an update's coefficients come from: n_part partials per vector (0: one
+// per `chunk` elements, chunk 0: one per update block), vectors maxP apart.
+struct GsSource {
+  const double2* partial;
+  int maxP, n_part, chunk;
+  __device__ int count(int64_t N, int elements) const {
+    const int c = chunk > 0 ? chunk : elements;
+    return n_part > 0 ? n_part : (int)((N + c - 1) / c);
+  }
+};
+
 // w -= sum_{i<nvec} h_i V_i with h_i the sum of the partials of the preceding
-// dots launch (n_part of them per vector; 0: one per part_chunk elements),
-// taken by every block in the same fixed order (block 0 also records them in
-// H: mode 0 H[i][j] = h_i, mode 1 H[i][j] += h_i).  A block takes nsub runs of
-// 64 elements in turn; its four waves take the vectors i = q mod 4 (q = wave)
-// and their sums are added in wave order.  With do_norm, each block also
-// writes its part of ||w||^2 to npart[b][block].
+// dots launch, taken by every block in the same fixed order (block 0 also
+// records them in H: mode 0 H[i][j] = h_i, mode 1 H[i][j] += h_i).  This form,
+// for short vectors: a block takes 64 elements; its four waves take the vectors
+// i = q mod 4 (q = wave) and their sums are added in wave order.  With do_norm,
+// each block also writes its part of ||w||^2 to npart[b][block].
 // KV > 0 folds the second Gram-Schmidt pass's inner products into the first
 // pass's update (nvec <= 4 KV): each wave keeps its KV basis entries of the
 // element in registers, and once the updated w is known forms conj(V_i) w for
 // them, so that the basis is streamed once for both; partial2[b][i][block]
-// receives the block's sums (fixed lane and run order).
-// Blocks (of nsub runs, nb_max per RHS) are work items strided over by the
-// grid, for the right-hand sides of rl (see rhs_count).
-// Dynamic LDS: nvec double2.
+// receives the block's sums (fixed lane order).
+template <int KV, typename VB, typename WB>
+__device__ __forceinline__ void gs_split_block(const VB* __restrict__ V, WB* __restrict__ w, const RhsVec r, int b,
+                                               int64_t blk, const RhsState* __restrict__ st, const GsSource src,
+                                               int nvec, int64_t ut, int do_norm, double* __restrict__ npart, int maxB,
+                                               double2* __restrict__ H, int m, int j, int mode,
+                                               double2* __restrict__ partial2, int maxP2, double2* hb,
+                                               double2 (&sh)[4], double2 (&part)[3][64], double2 (&wnew)[64]) {
+  const int e = threadIdx.x & 63, q = threadIdx.x >> 6;
+  __syncthreads();  // the previous item's reads of hb are done
+  sum_coefficients(src.partial + (size_t)b * nvec * src.maxP, src.maxP, src.count(r.N, 64), nvec, hb,
+                   blk == 0 ? H + (size_t)b * (m + 1) * m + j : nullptr, m, mode);
+  __syncthreads();
+  const bool act = st[b].active;
+  double nrm2 = 0.0;
+  double2 d2[KV > 0 ? KV : 1];
+#pragma unroll
+  for (int t = 0; t < (KV > 0 ? KV : 1); ++t) d2[t] = make_double2(0.0, 0.0);
+  const int64_t k = blk * 64 + e;
+  const bool live = k < r.N && act;
+  double2 acc = make_double2(0.0, 0.0);
+  // wave 0 reads w with the basis entries, so that the update after the
+  // barrier does not wait for memory
+  const double2 wpre = q == 0 && live ? ld_b(w + r.off + k) : make_double2(0.0, 0.0);
+  double2 vv[KV > 0 ? KV : 1];
+  if (KV > 0) {
+    if (live) {
+      const VB* vk = V + r.off + k;
+#pragma unroll
+      for (int t = 0; t < KV; ++t) {
+        const int i = q + 4 * t;
+        vv[t] = i < nvec ? ld_b(vk + (int64_t)i * ut) : make_double2(0.0, 0.0);
+      }
+#pragma unroll
+      for (int t = 0; t < KV; ++t) {
+        const int i = q + 4 * t;
+        if (i < nvec) {
+          const double2 c = cmul(hb[i], vv[t]);
+          acc.x += c.x;
+          acc.y += c.y;
+        }
+      }
+    }
+  } else if (live) {
+    const VB* vk = V + r.off + k;
+    int i = q;
+    for (; i + 12 < nvec; i += 16) {
+      const double2 v0 = ld_b(vk + (int64_t)i * ut), v1 = ld_b(vk + (int64_t)(i + 4) * ut);
+      const double2 v2 = ld_b(vk + (int64_t)(i + 8) * ut), v3 = ld_b(vk + (int64_t)(i + 12) * ut);
+      const double2 t0 = cmul(hb[i], v0), t1 = cmul(hb[i + 4], v1);
+      const double2 t2 = cmul(hb[i + 8], v2), t3 = cmul(hb[i + 12], v3);
+      acc.x += t0.x;
+      acc.y += t0.y;
+      acc.x += t1.x;
+      acc.y += t1.y;
+      acc.x += t2.x;
+      acc.y += t2.y;
+      acc.x += t3.x;
+      acc.y += t3.y;
+    }
+    for (; i < nvec; i += 4) {
+      const double2 t = cmul(hb[i], ld_b(vk + (int64_t)i * ut));
+      acc.x += t.x;
+      acc.y += t.y;
+    }
+  }
+  if (q > 0) part[q - 1][e] = acc;
+  __syncthreads();
+  if (q == 0 && live) {
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      acc.x += part[t][e].x;
+      acc.y += part[t][e].y;
+    }
+    double2 wk = wpre;
+    wk.x -= acc.x;
+    wk.y -= acc.y;
+    st_b(w + r.off + k, wk);
+    nrm2 += wk.x * wk.x + wk.y * wk.y;
+    if (KV > 0) wnew[e] = wk;
+  }
+  if (KV > 0) {
+    __syncthreads();
+    if (live) {
+      const double2 wk = wnew[e];
+#pragma unroll
+      for (int t = 0; t < KV; ++t) {
+        const double2 c = cmulc(vv[t], wk);
+        d2[t].x += c.x;
+        d2[t].y += c.y;
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < KV; ++t) {
+      double2 v = d2[t];
+      for (int o = 32; o >= 1; o >>= 1) {
+        v.x += __shfl_xor(v.x, o);
+        v.y += __shfl_xor(v.y, o);
+      }
+      const int i = q + 4 * t;
+      if (e == 0 && i < nvec) partial2[((size_t)b * nvec + i) * maxP2 + blk] = v;
+    }
+  }
+  if (do_norm) {
+    const double2 t = block_sum2(make_double2(nrm2, 0.0), sh);
+    if (threadIdx.x == 0) npart[(size_t)b * maxB + blk] = t.x;
+  }
+}
+
+// Blocks (nb_max per RHS) are work items strided over by the grid, for the
+// right-hand sides of rl (see rhs_count).  Dynamic LDS: nvec double2.
 template <int KV, typename VB, typename WB>
 __global__ void __launch_bounds__(256)
 gs_update_kernel(const VB* __restrict__ V, WB* __restrict__ w, const RhsVec* __restrict__ rv,
-                 const RhsState* __restrict__ st, const double2* __restrict__ partial, int maxP, int n_part,
-                 int nvec, int64_t ut, int do_norm, double* __restrict__ npart, int maxB, double2* __restrict__ H,
-                 int m, int j, int mode, const int* __restrict__ run_prev, const int* __restrict__ idle,
-                 int nsub, int part_chunk, double2* __restrict__ partial2, int maxP2, const int* __restrict__ rl,
-                 int B, int64_t nb_max) {
+                 const RhsState* __restrict__ st, GsSource src, int nvec, int64_t ut, int do_norm,
+                 double* __restrict__ npart, int maxB, double2* __restrict__ H, int m, int j, int mode,
+                 const int* __restrict__ run_prev, const int* __restrict__ idle, double2* __restrict__ partial2,
+                 int maxP2, const int* __restrict__ rl, int B, int64_t nb_max) {
   if (run_prev && *run_prev == 0) return;
   extern __shared__ double2 hb[];
   __shared__ double2 sh[4];
   __shared__ double2 part[3][64];
   __shared__ double2 wnew[64];
-  const int e = threadIdx.x & 63, q = threadIdx.x >> 6;
   const int64_t items = nb_max * rhs_count(rl, B);
   for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {  // uniform over the block
     const int li = (int)(item / nb_max);
@@ -556,140 +676,132 @@ gs_update_kernel(const VB* __restrict__ V, WB* __restrict__ w, const RhsVec* __r
     const int b = rhs_at(rl, li);
     if (!rl && idle && idle[b]) continue;
     const RhsVec r = rv[b];
-    const int64_t nb = (r.N + 64 * nsub - 1) / (64 * nsub);
-    if (blk >= nb) continue;
-    const int P = n_part > 0 ? n_part : (int)((r.N + part_chunk - 1) / part_chunk);
-    __syncthreads();  // the previous item's reads of hb are done
-    sum_coefficients(partial + (size_t)b * nvec * maxP, maxP, P, nvec, hb,
-                     blk == 0 ? H + (size_t)b * (m + 1) * m + j : nullptr, m, mode);
-    __syncthreads();
-    const bool act = st[b].active;
-    double nrm2 = 0.0;
-    double2 d2[KV > 0 ? KV : 1];
-#pragma unroll
-    for (int t = 0; t < (KV > 0 ? KV : 1); ++t) d2[t] = make_double2(0.0, 0.0);
-    for (int sb = 0; sb < nsub; ++sb) {  // uniform trip count: the barriers below are reached by all
-      const int64_t k = (blk * nsub + sb) * 64 + e;
-      const bool live = k < r.N && act;
-      double2 acc = make_double2(0.0, 0.0);
-      // wave 0 reads w with the basis entries, so that the update after the
-      // barrier does not wait for memory
-      const double2 wpre = q == 0 && live ? ld_b(w + r.off + k) : make_double2(0.0, 0.0);
-      double2 vv[KV > 0 ? KV : 1];
-      if (KV > 0) {
-        if (live) {
-          const VB* vk = V + r.off + k;
-#pragma unroll
-          for (int t = 0; t < KV; ++t) {
-            const int i = q + 4 * t;
-            vv[t] = i < nvec ? ld_b(vk + (int64_t)i * ut) : make_double2(0.0, 0.0);
-          }
-#pragma unroll
-          for (int t = 0; t < KV; ++t) {
-            const int i = q + 4 * t;
-            if (i < nvec) {
-              const double2 c = cmul(hb[i], vv[t]);
-              acc.x += c.x;
-              acc.y += c.y;
-            }
-          }
-        }
-      } else if (live) {
-        const VB* vk = V + r.off + k;
-        int i = q;
-        for (; i + 12 < nvec; i += 16) {
-          const double2 v0 = ld_b(vk + (int64_t)i * ut), v1 = ld_b(vk + (int64_t)(i + 4) * ut);
-          const double2 v2 = ld_b(vk + (int64_t)(i + 8) * ut), v3 = ld_b(vk + (int64_t)(i + 12) * ut);
-          const double2 t0 = cmul(hb[i], v0), t1 = cmul(hb[i + 4], v1);
-          const double2 t2 = cmul(hb[i + 8], v2), t3 = cmul(hb[i + 12], v3);
-          acc.x += t0.x;
-          acc.y += t0.y;
-          acc.x += t1.x;
-          acc.y += t1.y;
-          acc.x += t2.x;
-          acc.y += t2.y;
-          acc.x += t3.x;
-          acc.y += t3.y;
-        }
-        for (; i < nvec; i += 4) {
-          const double2 t = cmul(hb[i], ld_b(vk + (int64_t)i * ut));
-          acc.x += t.x;
-          acc.y += t.y;
-        }
-      }
-      if (q > 0) part[q - 1][e] = acc;
-      __syncthreads();
-      if (q == 0 && live) {
-#pragma unroll
-        for (int t = 0; t < 3; ++t) {
-          acc.x += part[t][e].x;
-          acc.y += part[t][e].y;
-        }
-        double2 wk = wpre;
-        wk.x -= acc.x;
-        wk.y -= acc.y;
-        st_b(w + r.off + k, wk);
-        nrm2 += wk.x * wk.x + wk.y * wk.y;
-        if (KV > 0) wnew[e] = wk;
-      }
-      __syncthreads();  // part (and wnew) are reused by the next run
-      if (KV > 0 && live) {
-        // (the next run writes wnew only after its first barrier, which every
-        // wave reaches after these reads)
-        const double2 wk = wnew[e];
-#pragma unroll
-        for (int t = 0; t < KV; ++t) {
-          const double2 c = cmulc(vv[t], wk);
-          d2[t].x += c.x;
-          d2[t].y += c.y;
-        }
-      }
-    }
-    if (KV > 0) {
-#pragma unroll
-      for (int t = 0; t < KV; ++t) {
-        double2 v = d2[t];
-        for (int o = 32; o >= 1; o >>= 1) {
-          v.x += __shfl_xor(v.x, o);
-          v.y += __shfl_xor(v.y, o);
-        }
-        const int i = q + 4 * t;
-        if (e == 0 && i < nvec) partial2[((size_t)b * nvec + i) * maxP2 + blk] = v;
-      }
-    }
-    if (do_norm) {
-      const double2 t = block_sum2(make_double2(nrm2, 0.0), sh);
-      if (threadIdx.x == 0) npart[(size_t)b * maxB + blk] = t.x;
-    }
+    if (blk >= (r.N + 63) / 64) continue;
+    gs_split_block<KV>(V, w, r, b, blk, st, src, nvec, ut, do_norm, npart, maxB, H, m, j, mode, partial2, maxP2, hb, sh,
+                       part, wnew);
   }
 }
 
-// The update of gs_update_kernel for long vectors (blocks of four 64-element
-// runs): every thread takes its own element of the block and loops over the
+// The update of gs_update_kernel for long vectors: blocks of 256 elements, every
+// thread takes its own element of the block and loops over the
 // basis vectors (loads issued in groups before the products), so that all
 // four waves stream at every basis size.  NV > 0 folds the second pass's
 // inner products (nvec <= NV <= kFoldMaxVecEl, NV a power of two up to 16 or
 // 20, 24 or 32): the element's basis entries
 // stay in registers, each wave sums conj(V_i) w over its lanes
 // (wave_transpose_sum) and the block adds the waves in a fixed order into
-// partial2[b][i][block].  Same arguments and outputs as gs_update_kernel with
-// nsub = 4.  skip (nullable; a second pass, mode 1): the pass leaves w, its
-// norm parts and H alone for every RHS with skip[b] != 0 (finish_norm_kernel).
+// partial2[b][i][block].  Same arguments and outputs as gs_update_kernel.
+// skip (nullable; a second pass, mode 1): the pass leaves w, its norm parts and
+// H alone for every RHS with skip[b] != 0 (finish_norm_kernel).
+template <int NV, typename VB, typename WB>
+__device__ __forceinline__ void gs_element_block(const VB* __restrict__ V, WB* __restrict__ w, const RhsVec r, int b,
+                                                 int64_t blk, const RhsState* __restrict__ st, const GsSource src,
+                                                 int nvec, int64_t ut, int do_norm, double* __restrict__ npart,
+                                                 int maxB, double2* __restrict__ H, int m, int j, int mode,
+                                                 double2* __restrict__ partial2, int maxP2, double2* hb,
+                                                 double2 (&sh)[4], double2 (&red)[4][NV > 0 ? NV : 1]) {
+  constexpr bool FOLD = NV > 0;
+  constexpr int kEl = 256;  // elements per block
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // this item's element of w and of the basis (the first 8 vectors without
+  // folding) are loaded before the coefficient sums, which do not need them
+  const int64_t k = blk * kEl + tid;
+  const bool live = k < r.N && st[b].active;
+  double2 wk = live ? ld_b(w + r.off + k) : make_double2(0.0, 0.0);
+  VB vv[FOLD ? NV : 8];
+  const VB* vk = V + r.off + k;
+  if (live) {
+#pragma unroll
+    for (int i = 0; i < (FOLD ? NV : 8); ++i)
+      if (i < nvec) vv[i] = vk[(int64_t)i * ut];
+  }
+  __syncthreads();  // the previous item's reads of hb and red are done
+  sum_coefficients(src.partial + (size_t)b * nvec * src.maxP, src.maxP, src.count(r.N, kEl), nvec, hb,
+                   blk == 0 ? H + (size_t)b * (m + 1) * m + j : nullptr, m, mode);
+  __syncthreads();
+  double nrm2 = 0.0;
+  if (live) {
+    double2 acc = make_double2(0.0, 0.0);
+    if (FOLD) {
+#pragma unroll
+      for (int i = 0; i < (FOLD ? NV : 8); ++i)
+        if (i < nvec) {
+          const double2 c = cmul(hb[i], to_d2(vv[i]));
+          acc.x += c.x;
+          acc.y += c.y;
+        }
+    } else {
+      for (int i0 = 0; i0 < nvec; i0 += 8) {
+        if (i0 > 0) {  // the first 8 were loaded above
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            if (i0 + u < nvec) vv[u] = vk[(int64_t)(i0 + u) * ut];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (i0 + u < nvec) {
+            const double2 c = cmul(hb[i0 + u], to_d2(vv[u]));
+            acc.x += c.x;
+            acc.y += c.y;
+          }
+      }
+    }
+    wk.x -= acc.x;
+    wk.y -= acc.y;
+    st_b(w + r.off + k, wk);
+    nrm2 = wk.x * wk.x + wk.y * wk.y;
+  }
+  if (FOLD) {
+    constexpr int NF = FOLD ? NV : 1;
+    auto dot = [&](int i) {
+      return (live && i < nvec && i < NF) ? cmulc(to_d2(vv[i < NF ? i : 0]), wk) : make_double2(0.0, 0.0);
+    };
+    // the first (up to) 16 products, then the rest padded to a power of
+    // two (fewer live registers than one sum over all of them)
+    auto fold_sum = [&](auto nh_c, int h0) {
+      constexpr int NH = decltype(nh_c)::value;
+      constexpr int sh_v = NH == 1 ? 6 : NH == 2 ? 5 : NH == 4 ? 4 : NH == 8 ? 3 : 2;
+      double2 d[NH];
+#pragma unroll
+      for (int i = 0; i < NH; ++i) d[i] = dot(h0 + i);
+      wave_transpose_sum<NH>(d, lane);
+      const int vi = h0 + (lane >> sh_v);  // the value this lane holds the total of
+      if ((lane & ((1 << sh_v) - 1)) == 0 && vi < nvec) red[wave][vi] = d[0];
+    };
+    constexpr int NA = NF > 16 ? 16 : NF, NR = NF - NA;
+    constexpr int NB = NR == 0 ? 1 : NR <= 2 ? 2 : NR <= 4 ? 4 : NR <= 8 ? 8 : 16;
+    fold_sum(std::integral_constant<int, NA>(), 0);
+    if constexpr (NR > 0) {
+      if (nvec > 16) fold_sum(std::integral_constant<int, NB>(), 16);  // uniform
+    }
+    __syncthreads();
+    if (tid < nvec) {
+      double2 t = red[0][tid];
+#pragma unroll
+      for (int q = 1; q < 4; ++q) {
+        t.x += red[q][tid].x;
+        t.y += red[q][tid].y;
+      }
+      partial2[((size_t)b * nvec + tid) * maxP2 + blk] = t;
+    }
+  }
+  if (do_norm) {
+    const double2 t = block_sum2(make_double2(nrm2, 0.0), sh);
+    if (tid == 0) npart[(size_t)b * maxB + blk] = t.x;
+  }
+}
+
 template <int NV, typename VB, typename WB>
 __global__ void __launch_bounds__(256, NV == 20 ? 4 : 1)
 gs_update_el_kernel(const VB* __restrict__ V, WB* __restrict__ w, const RhsVec* __restrict__ rv,
-                    const RhsState* __restrict__ st, const double2* __restrict__ partial, int maxP, int n_part,
-                    int nvec, int64_t ut, int do_norm, double* __restrict__ npart, int maxB,
-                    double2* __restrict__ H, int m, int j, int mode, const int* __restrict__ run_prev,
-                    const int* __restrict__ idle, int part_chunk, double2* __restrict__ partial2, int maxP2,
-                    const int* __restrict__ rl, int B, int64_t nb_max, const double* __restrict__ skip) {
+                    const RhsState* __restrict__ st, GsSource src, int nvec, int64_t ut, int do_norm,
+                    double* __restrict__ npart, int maxB, double2* __restrict__ H, int m, int j, int mode,
+                    const int* __restrict__ run_prev, const int* __restrict__ idle, double2* __restrict__ partial2,
+                    int maxP2, const int* __restrict__ rl, int B, int64_t nb_max, const double* __restrict__ skip) {
   if (run_prev && *run_prev == 0) return;
-  constexpr bool FOLD = NV > 0;
-  constexpr int kEl = 256;  // elements per block: four 64-element runs
   extern __shared__ double2 hb[];
   __shared__ double2 sh[4];
-  __shared__ double2 red[4][FOLD ? NV : 1];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ double2 red[4][NV > 0 ? NV : 1];
   const int64_t items = nb_max * rhs_count(rl, B);
   for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {  // uniform over the block
     const int li = (int)(item / nb_max);
@@ -697,96 +809,46 @@ gs_update_el_kernel(const VB* __restrict__ V, WB* __restrict__ w, const RhsVec* 
     const int b = rhs_at(rl, li);
     if (!rl && idle && idle[b]) continue;
     const RhsVec r = rv[b];
-    const int64_t nb = (r.N + kEl - 1) / kEl;
-    if (blk >= nb) continue;
+    if (blk >= (r.N + 255) / 256) continue;
     if (skip && skip[b] != 0.0) continue;
-    const int P = n_part > 0 ? n_part : (int)((r.N + part_chunk - 1) / part_chunk);
-    // this item's element of w and of the basis (the first 8 vectors without
-    // folding) are loaded before the coefficient sums, which do not need them
-    const int64_t k = blk * kEl + tid;
-    const bool live = k < r.N && st[b].active;
-    double2 wk = live ? ld_b(w + r.off + k) : make_double2(0.0, 0.0);
-    VB vv[FOLD ? NV : 8];
-    const VB* vk = V + r.off + k;
-    if (live) {
-#pragma unroll
-      for (int i = 0; i < (FOLD ? NV : 8); ++i)
-        if (i < nvec) vv[i] = vk[(int64_t)i * ut];
-    }
-    __syncthreads();  // the previous item's reads of hb and red are done
-    sum_coefficients(partial + (size_t)b * nvec * maxP, maxP, P, nvec, hb,
-                     blk == 0 ? H + (size_t)b * (m + 1) * m + j : nullptr, m, mode);
-    __syncthreads();
-    double nrm2 = 0.0;
-    if (live) {
-      double2 acc = make_double2(0.0, 0.0);
-      if (FOLD) {
-#pragma unroll
-        for (int i = 0; i < (FOLD ? NV : 8); ++i)
-          if (i < nvec) {
-            const double2 c = cmul(hb[i], to_d2(vv[i]));
-            acc.x += c.x;
-            acc.y += c.y;
-          }
-      } else {
-        for (int i0 = 0; i0 < nvec; i0 += 8) {
-          if (i0 > 0) {  // the first 8 were loaded above
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-              if (i0 + u < nvec) vv[u] = vk[(int64_t)(i0 + u) * ut];
-          }
-#pragma unroll
-          for (int u = 0; u < 8; ++u)
-            if (i0 + u < nvec) {
-              const double2 c = cmul(hb[i0 + u], to_d2(vv[u]));
-              acc.x += c.x;
-              acc.y += c.y;
-            }
-        }
-      }
-      wk.x -= acc.x;
-      wk.y -= acc.y;
-      st_b(w + r.off + k, wk);
-      nrm2 = wk.x * wk.x + wk.y * wk.y;
-    }
-    if (FOLD) {
-      constexpr int NF = FOLD ? NV : 1;
-      auto dot = [&](int i) {
-        return (live && i < nvec && i < NF) ? cmulc(to_d2(vv[i < NF ? i : 0]), wk) : make_double2(0.0, 0.0);
-      };
-      // the first (up to) 16 products, then the rest padded to a power of
-      // two (fewer live registers than one sum over all of them)
-      auto fold_sum = [&](auto nh_c, int h0) {
-        constexpr int NH = decltype(nh_c)::value;
-        constexpr int sh_v = NH == 1 ? 6 : NH == 2 ? 5 : NH == 4 ? 4 : NH == 8 ? 3 : 2;
-        double2 d[NH];
-#pragma unroll
-        for (int i = 0; i < NH; ++i) d[i] = dot(h0 + i);
-        wave_transpose_sum<NH>(d, lane);
-        const int vi = h0 + (lane >> sh_v);  // the value this lane holds the total of
-        if ((lane & ((1 << sh_v) - 1)) == 0 && vi < nvec) red[wave][vi] = d[0];
-      };
-      constexpr int NA = NF > 16 ? 16 : NF, NR = NF - NA;
-      constexpr int NB = NR == 0 ? 1 : NR <= 2 ? 2 : NR <= 4 ? 4 : NR <= 8 ? 8 : 16;
-      fold_sum(std::integral_constant<int, NA>(), 0);
-      if constexpr (NR > 0) {
-        if (nvec > 16) fold_sum(std::integral_constant<int, NB>(), 16);  // uniform
-      }
-      __syncthreads();
-      if (tid < nvec) {
-        double2 t = red[0][tid];
-#pragma unroll
-        for (int q = 1; q < 4; ++q) {
-          t.x += red[q][tid].x;
-          t.y += red[q][tid].y;
-        }
-        partial2[((size_t)b * nvec + tid) * maxP2 + blk] = t;
-      }
-    }
-    if (do_norm) {
-      const double2 t = block_sum2(make_double2(nrm2, 0.0), sh);
-      if (tid == 0) npart[(size_t)b * maxB + blk] = t.x;
-    }
+    gs_element_block<NV>(V, w, r, b, blk, st, src, nvec, ut, do_norm, npart, maxB, H, m, j, mode, partial2, maxP2, hb,
+                         sh, red);
+  }
+}
+
+// Batches with vectors on both sides of `line`: each right-hand side in its own
+// form, one launch (a second one would cost small solves as much as an update
+// itself).  src_s, src_l: where the short and the long ones take their
+// coefficients from; rows of partial2 are maxP2 apart for both.
+template <int NV, int KV, typename VB, typename WB>
+__global__ void __launch_bounds__(256, NV == 20 ? 4 : 1)
+gs_update_mixed_kernel(const VB* __restrict__ V, WB* __restrict__ w, const RhsVec* __restrict__ rv,
+                       const RhsState* __restrict__ st, GsSource src_s, GsSource src_l, int nvec, int64_t ut,
+                       int do_norm, double* __restrict__ npart, int maxB, double2* __restrict__ H, int m, int j,
+                       int mode, const int* __restrict__ run_prev, const int* __restrict__ idle,
+                       double2* __restrict__ partial2, int maxP2, const int* __restrict__ rl, int B, int64_t nb_max,
+                       int64_t line) {
+  if (run_prev && *run_prev == 0) return;
+  extern __shared__ double2 hb[];
+  __shared__ double2 sh[4];
+  __shared__ double2 part[3][64];
+  __shared__ double2 wnew[64];
+  __shared__ double2 red[4][NV > 0 ? NV : 1];
+  const int64_t items = nb_max * rhs_count(rl, B);
+  for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {  // uniform over the block
+    const int li = (int)(item / nb_max);
+    const int64_t blk = item - li * nb_max;
+    const int b = rhs_at(rl, li);
+    if (!rl && idle && idle[b]) continue;
+    const RhsVec r = rv[b];
+    const int el = update_elements(r.N, line);
+    if (blk >= (r.N + el - 1) / el) continue;
+    if (r.N > line)
+      gs_element_block<NV>(V, w, r, b, blk, st, src_l, nvec, ut, do_norm, npart, maxB, H, m, j, mode, partial2, maxP2,
+                           hb, sh, red);
+    else
+      gs_split_block<KV>(V, w, r, b, blk, st, src_s, nvec, ut, do_norm, npart, maxB, H, m, j, mode, partial2, maxP2,
+                         hb, sh, part, wnew);
   }
 }
 
@@ -801,9 +863,9 @@ bool selective_cgs2() {
   return sel;
 }
 
-// ||w|| from the per-block parts of the preceding update (one per part_el
-// elements; 0: one in all), summed by every block in the same fixed
-// order; block 0 sets H[j+1][j] = ||w|| and
+// ||w|| from the per-block parts of the preceding update (summed: one in all,
+// else those of the form that `line` gives the RHS), summed by every block in
+// the same fixed order; block 0 sets H[j+1][j] = ||w|| and
 // applies the Givens step; every block writes V_{j+1} = w / ||w|| (zeros for
 // a finished RHS or a breakdown) and, for the next step's matvec, its input
 // in the store precision OT: V_{j+1} itself (MODE 1) or M^{-1} V_{j+1}
@@ -817,7 +879,7 @@ bool selective_cgs2() {
 template <typename OT, int MODE, typename VB, typename WB, int RW = 1>
 __global__ void __launch_bounds__(256)
 normalize_step_kernel(const WB* __restrict__ w, VB* __restrict__ V, const RhsVec* __restrict__ rv,
-                      RhsState* __restrict__ st, const double* __restrict__ npart, int maxB, int part_el,
+                      RhsState* __restrict__ st, const double* __restrict__ npart, int maxB, int summed, int64_t line,
                       double2* __restrict__ H, double2* __restrict__ g, double* __restrict__ cs,
                       double2* __restrict__ sn, int m, int j, double tol, int* __restrict__ n_running,
                       double* __restrict__ wn, int64_t ut, const int* __restrict__ live,
@@ -856,7 +918,8 @@ normalize_step_kernel(const WB* __restrict__ w, VB* __restrict__ V, const RhsVec
     if (blk * RW * blockDim.x >= r.N) continue;  // uniform over the block
     __syncthreads();  // the previous item's reads of nv_s and v_s are done
     if (threadIdx.x < 64) {
-      const double sum = wave_sum_partials(npart + (size_t)b * maxB, part_el > 0 ? (int)((r.N + part_el - 1) / part_el) : 1);
+      const int el = update_elements(r.N, line);
+      const double sum = wave_sum_partials(npart + (size_t)b * maxB, summed ? 1 : (int)((r.N + el - 1) / el));
       if (threadIdx.x == 0) nv_s = sqrt(fmax(sum, 0.0));
     }
     __syncthreads();
@@ -1394,26 +1457,32 @@ struct Work {
 
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
-// 64-element runs per update block: four, with every thread on its own
-// element (gs_update_el_kernel), or one, whose four waves share the basis
-// vectors of its 64 elements (gs_update_kernel; short vectors then fill four
-// times the workgroups).  The line was drawn from whole solves (ms, split /
+// The update's form of a right-hand side of N unknowns: above the line 256
+// elements a block, every thread on its own (gs_element_block), else 64, whose
+// four waves share the basis vectors (gs_split_block; short vectors then fill
+// four times the workgroups).  The line was drawn from whole solves (ms, split /
 // element form; 1-bit arrays of N unknowns):
-//   complex64 basis, GMRES(20): N = 5,760 1.74 / 1.77 (1 RHS), 3.20 / 3.02
-//   (32 RHS); 10,240 2.33 / 2.32, 5.15 / 4.58; 40,960 7.04 / 6.89, 31.9 / 26.6
-//   (with FP64 refinement 37.3 / 28.0);
-//   complex128 basis, GMRES(60), no preconditioner: 1,440 20.6 / 22.2 (1 RHS),
-//   32.8 / 34.4 (16 RHS); 10,240 199 / 202; 23,040 even.
-// It depends on the longest vector of the batch and not on its width.
-int update_runs(int64_t maxN, bool vb32) { return maxN > (vb32 ? kElementMin32 : kElementMin64) ? 4 : 1; }
-// basis vectors a folded update takes: the element-parallel kernel (long
-// vectors) holds more
-int fold_max_vec(int64_t maxN, bool vb32) {
-  return update_runs(maxN, vb32) == 4 && vb32 ? kFoldMaxVecEl : kFoldMaxVec;
+//   complex64 basis, FP64 refinement, GMRES(20): N = 4,000 4.23 / 4.22 (1 RHS),
+//   6.45 / 6.14 (32 RHS), 5,760 4.96 / 5.03, 7.69 / 7.07, 7,840 5.35 / 5.41, 9.66 /
+//   8.53; 40,960 37.3 / 28.0 (24 RHS);
+//   complex128 basis, GMRES(20): 5,760 2.25 / 2.27 (1 RHS), 2.77 / 2.74 (8 RHS);
+//   10,240 2.80 / 2.80, 3.83 / 3.74; 16,000 6.66 / 6.70, 10.83 / 10.42; GMRES(60):
+//   5,760 2.12 / 2.17, 10,240 2.73 / 2.78; relaxed solves of 5,760 20.3 / 20.8.
+// Each right-hand side is judged by its own length, so that a solve gives the
+// same bits alone and beside others.  Batches with a vector of more than 64
+// chunks of kDotChunk take the element form throughout, with the selective
+// second pass (and one launch that sums the partials for all).
+int64_t element_line(int64_t maxN, bool vb32) {
+  if ((maxN + kDotChunk - 1) / kDotChunk > kPartialsInUpdate) return 0;
+  return vb32 ? kElementMin32 : kElementMin64;
 }
-int64_t fold_blocks(int64_t maxN, bool vb32) {
-  const int nsub = update_runs(maxN, vb32);
-  return std::max<int64_t>(1, (maxN + 64 * nsub - 1) / (64 * nsub));
+// basis vectors a folded update takes: the element-parallel form holds more
+int fold_max_vec(bool element, bool vb32) { return element && vb32 ? kFoldMaxVecEl : kFoldMaxVec; }
+// partials per vector of a folded update of up to maxN unknowns, of a batch
+// with (both) or without vectors below the line beside longer ones
+int64_t fold_blocks(int64_t maxN, int64_t line, bool both) {
+  const int64_t el = update_elements(maxN, line), n = std::max<int64_t>(1, (maxN + el - 1) / el);
+  return both ? std::max<int64_t>(n, (line + 63) / 64) : n;
 }
 
 // n_blocks: block-Jacobi inverses held (one per state, or one per unit for
@@ -1422,8 +1491,13 @@ Work layout_work(char* base, const BatchDesc& bd, int n_a, int n_blocks, int m, 
                  size_t lists_bytes, size_t lists64_bytes, size_t ilu_bytes, bool vb32) {
   Work w{};
   const int B = bd.B;
-  int64_t maxN = 0;
-  for (int b = 0; b < B; ++b) maxN = std::max<int64_t>(maxN, bd.n_units[b] * n_a);
+  int64_t maxN = 0, minN = INT64_MAX;
+  for (int b = 0; b < B; ++b) {
+    maxN = std::max<int64_t>(maxN, bd.n_units[b] * n_a);
+    minN = std::min<int64_t>(minN, bd.n_units[b] * n_a);
+  }
+  const int64_t line = element_line(maxN, vb32);
+  const bool both = minN <= line && maxN > line;
   const size_t ut = (size_t)bd.total_units * n_a;
   const int64_t vtot = (int64_t)(m + 1) * ut;
   const int maxP = (int)((maxN + kDotChunk - 1) / kDotChunk);
@@ -1452,7 +1526,9 @@ Work layout_work(char* base, const BatchDesc& bd, int n_a, int n_blocks, int m, 
   w.cs = (double*)take((size_t)B * m * 8);
   w.sn = (double2*)take((size_t)B * m * 16);
   w.dpart = (double2*)take((size_t)B * (m + 1) * std::max(maxP, 1) * 16);
-  w.dpart2 = (double2*)take((size_t)B * std::min(m + 1, fold_max_vec(maxN, vb32)) * fold_blocks(maxN, vb32) * 16);
+  w.dpart2 = (double2*)take((size_t)B * 16 *
+                            std::max(std::min(m + 1, fold_max_vec(maxN > line, vb32)) * fold_blocks(maxN, line, false),
+                                     std::min(m + 1, kFoldMaxVec) * fold_blocks(maxN, line, both)));
   w.hbuf = (double2*)take((size_t)B * (m + 1) * 16);
   w.hsum = (double2*)take((size_t)B * (m + 1) * 16);
   w.nsum = (double*)take((size_t)B * 8);
@@ -1485,7 +1561,7 @@ struct GmresRun {
   int ilu_r = 0;                // > 0: the near-field block ILU(0) of this radius preconditions
   bool vb32 = false;            // the Krylov basis W.V holds complex64 (see basis32)
   int G = 1;  // displacement groups of the matvec (autotuned)
-  int64_t maxN, ut;
+  int64_t maxN, minN, ut;
   Work W;
   hipStream_t s;
 
@@ -1638,19 +1714,22 @@ struct GmresRun {
     // long vectors (more than 64 chunk partials per coefficient): sum the
     // partials once in their own launch rather than in every update block
     const bool long_vec = maxP > kPartialsInUpdate;
-    const int nsub = update_runs(maxN, sizeof(VB) == sizeof(float2));
+    // the updates' forms (see element_line)
+    constexpr bool vb4 = sizeof(VB) == sizeof(float2);
+    const int64_t line = element_line(maxN, vb4);
+    const bool el = maxN > line, both = el && minN <= line;
     const int nvec = j + 1;
     // inner-product items of dv vectors: the basis count padded to a power of
     // two up to dot_vec (the exchanges of the lane sums scale with dv)
     const int dv = std::min(dot_vec<VB>(), nvec <= 1 ? 1 : nvec <= 2 ? 2 : nvec <= 4 ? 4 : 8);
     const int ngrp = (nvec + dv - 1) / dv;
-    const int64_t nb_u = (maxN + 64 * nsub - 1) / (64 * nsub);
+    const int64_t nb_u = fold_blocks(maxN, line, both);
     const unsigned dgrid = stride_grid((int64_t)maxP * ngrp * B), ugrid = stride_grid(nb_u * B);
     const size_t ulds = (size_t)nvec * sizeof(double2);
-    auto dots = [&](int* reset) {
+    auto dots = [&](int* reset, int64_t most) {
       auto go = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3(dgrid), dim3(kDotThreads), 0, s, V, ut, wv, W.rv, nvec, maxP, W.dpart, reset,
-                           live, W.idle, rl, B);
+                           live, W.idle, rl, B, most);
       };
       if (dv == 1)
         go(dots_partials_kernel<VB, WB, 1>);
@@ -1661,84 +1740,91 @@ struct GmresRun {
       else
         go(dots_partials_kernel<VB, WB, dot_vec<VB>()>);
     };
-    // CGS2, first pass: inner products with the basis, then the update
-    dots(run_slot(j));
-    if (long_vec)
-      hipLaunchKernelGGL(finish_partials_kernel, dim3((nvec + 3) / 4, B), dim3(256), 0, s, (const double2*)W.dpart, maxP, nvec,
-                         W.rv, W.hsum, live, W.idle, kDotChunk);
-    const double2* h0 = long_vec ? (const double2*)W.hsum : (const double2*)W.dpart;
-    const int h0P = long_vec ? 1 : maxP, h0n = long_vec ? 1 : 0;
-    // one Gram-Schmidt update (kv > 0: folding the second pass's inner
-    // products): the element-parallel kernel for long vectors
-    auto update = [&](int kv, const double2* hp, int hP, int hn, int do_norm, int mode, int pchunk, double2* p2,
-                      int mP2, const double* skip) {
-      R3M_REQUIRE(!skip || (nsub == 4 && kv == 0), R3M_ERR_UNSUPPORTED, "selective second pass on the element kernel");
-      auto el = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3(ugrid), dim3(256), ulds, s, V, wv, W.rv, W.st, hp, hP, hn, nvec, ut, do_norm,
-                           W.npart, maxB, W.H, m, j, mode, live, W.idle, pchunk, p2, mP2, rl, B, nb_u, skip);
-      };
-      if (nsub == 4 && kv > 0) {
-        // the basis count padded to a power of two
-        if (nvec <= 2)
-          el(gs_update_el_kernel<2, VB, WB>);
-        else if (nvec <= 4)
-          el(gs_update_el_kernel<4, VB, WB>);
-        else if (nvec <= 8)
-          el(gs_update_el_kernel<8, VB, WB>);
-        else if (nvec <= 16 || sizeof(VB) != sizeof(float2))
-          el(gs_update_el_kernel<16, VB, WB>);
-        else if (nvec <= 20)
-          el(gs_update_el_kernel<20, VB, WB>);
-        else if (nvec <= 24)
-          el(gs_update_el_kernel<24, VB, WB>);
-        else
-          el(gs_update_el_kernel<32, VB, WB>);
-      } else if (nsub == 4)
-        el(gs_update_el_kernel<0, VB, WB>);
-      else if (kv == 2)
-        hipLaunchKernelGGL((gs_update_kernel<2, VB, WB>), dim3(ugrid), dim3(256), ulds, s, V, wv, W.rv, W.st, hp, hP,
-                           hn, nvec, ut, do_norm, W.npart, maxB, W.H, m, j, mode, live, W.idle, nsub, pchunk, p2, mP2,
-                           rl, B, nb_u);
-      else if (kv == 4)
-        hipLaunchKernelGGL((gs_update_kernel<4, VB, WB>), dim3(ugrid), dim3(256), ulds, s, V, wv, W.rv, W.st, hp, hP,
-                           hn, nvec, ut, do_norm, W.npart, maxB, W.H, m, j, mode, live, W.idle, nsub, pchunk, p2, mP2,
-                           rl, B, nb_u);
-      else
-        hipLaunchKernelGGL((gs_update_kernel<0, VB, WB>), dim3(ugrid), dim3(256), ulds, s, V, wv, W.rv, W.st, hp, hP,
-                           hn, nvec, ut, do_norm, W.npart, maxB, W.H, m, j, mode, live, W.idle, nsub, pchunk, p2, mP2,
-                           rl, B, nb_u);
+    auto finish = [&](const double2* partial, int mP, int chunk) {
+      hipLaunchKernelGGL(finish_partials_kernel, dim3((nvec + 3) / 4, B), dim3(256), 0, s, partial, mP, nvec, W.rv,
+                         W.hsum, live, W.idle, chunk, line);
     };
-    if (nvec <= fold_max_vec(maxN, sizeof(VB) == sizeof(float2)) && W.dpart2) {
+    // CGS2, first pass: inner products with the basis, then the update
+    dots(run_slot(j), INT64_MAX);
+    if (long_vec) finish(W.dpart, maxP, kDotChunk);
+    const GsSource summed{W.hsum, 1, 1, 0}, chunks = long_vec ? summed : GsSource{W.dpart, maxP, 0, kDotChunk};
+    // one Gram-Schmidt update.  fold: the long and the short vectors also form
+    // the second pass's inner products; from: the coefficients of either
+    const int maxP2 = (int)fold_blocks(maxN, line, both && nvec <= kFoldMaxVec);
+    auto update = [&](bool fold_l, bool fold_s, const GsSource& from_l, const GsSource& from_s, int do_norm, int mode,
+                      const double* skip) {
+      R3M_REQUIRE(!skip || (el && !both && !fold_l), R3M_ERR_UNSUPPORTED,
+                  "selective second pass on the element form");
+      auto go = [&](auto nv_c, auto kv_c) {
+        constexpr int NV = decltype(nv_c)::value, KV = decltype(kv_c)::value;
+        if (both)
+          hipLaunchKernelGGL((gs_update_mixed_kernel<NV, KV, VB, WB>), dim3(ugrid), dim3(256), ulds, s, V, wv, W.rv,
+                             W.st, from_s, from_l, nvec, ut, do_norm, W.npart, maxB, W.H, m, j, mode, live, W.idle,
+                             W.dpart2, maxP2, rl, B, nb_u, line);
+        else if (el)
+          hipLaunchKernelGGL((gs_update_el_kernel<NV, VB, WB>), dim3(ugrid), dim3(256), ulds, s, V, wv, W.rv, W.st,
+                             from_l, nvec, ut, do_norm, W.npart, maxB, W.H, m, j, mode, live, W.idle, W.dpart2, maxP2,
+                             rl, B, nb_u, skip);
+        else
+          hipLaunchKernelGGL((gs_update_kernel<KV, VB, WB>), dim3(ugrid), dim3(256), ulds, s, V, wv, W.rv, W.st,
+                             from_s, nvec, ut, do_norm, W.npart, maxB, W.H, m, j, mode, live, W.idle, W.dpart2, maxP2,
+                             rl, B, nb_u);
+      };
+      using std::integral_constant;
+      // element form: the basis count padded to a power of two; split form:
+      // four vectors a wave and register
+      if (fold_l && !fold_s) {
+        if constexpr (vb4) {
+          if (nvec <= 20)
+            go(integral_constant<int, 20>(), integral_constant<int, 0>());
+          else if (nvec <= 24)
+            go(integral_constant<int, 24>(), integral_constant<int, 0>());
+          else
+            go(integral_constant<int, 32>(), integral_constant<int, 0>());
+        }
+      } else if (fold_s) {
+        if (nvec <= 2)
+          go(integral_constant<int, 2>(), integral_constant<int, 2>());
+        else if (nvec <= 4)
+          go(integral_constant<int, 4>(), integral_constant<int, 2>());
+        else if (nvec <= 8)
+          go(integral_constant<int, 8>(), integral_constant<int, 2>());
+        else
+          go(integral_constant<int, 16>(), integral_constant<int, 4>());
+      } else {
+        go(integral_constant<int, 0>(), integral_constant<int, 0>());
+      }
+    };
+    // (a form's own limit: up to kFoldMaxVec vectors both fold)
+    const bool fold_s = nvec <= kFoldMaxVec, fold_l = fold_s || (el && nvec <= fold_max_vec(true, vb4));
+    if (fold_l) {
       // the first update also forms the second pass's inner products; on
       // long vectors it also takes ||w||^2, and the second pass runs only
       // where the first does not suffice (the first pass's norm parts then
       // stand for the RHS that skip it)
-      const int maxP2 = (int)fold_blocks(maxN, sizeof(VB) == sizeof(float2));
-      const bool sel = long_vec && nsub == 4 && selective_cgs2();
-      update(nvec <= 8 ? 2 : 4, h0, h0P, h0n, sel ? 1 : 0, 0, kDotChunk, W.dpart2, maxP2, nullptr);
+      const bool sel = long_vec && selective_cgs2();
+      update(true, fold_s, chunks, chunks, sel ? 1 : 0, 0, nullptr);
       if (sel)
         hipLaunchKernelGGL(finish_norm_kernel, dim3(B), dim3(256), 0, s, (const double*)W.npart, maxB, W.rv, W.nsum,
-                           live, W.idle, nsub, (const double2*)W.H, m, j, nvec);
+                           live, W.idle, (const double2*)W.H, m, j, nvec);
       const bool fin2 = long_vec || maxP2 > kPartials2InUpdate;
-      if (fin2)
-        hipLaunchKernelGGL(finish_partials_kernel, dim3((nvec + 3) / 4, B), dim3(256), 0, s, (const double2*)W.dpart2,
-                           maxP2, nvec, W.rv, W.hsum, live, W.idle, 64 * nsub);
-      update(0, fin2 ? (const double2*)W.hsum : (const double2*)W.dpart2, fin2 ? 1 : maxP2, fin2 ? 1 : 0, 1, 1,
-             64 * nsub, (double2*)nullptr, 0, sel ? (const double*)W.nsum : nullptr);
+      if (fin2) finish(W.dpart2, maxP2, 0);
+      const GsSource folded = fin2 ? summed : GsSource{W.dpart2, maxP2, 0, 0};
+      // the short vectors of a mixed batch past their limit: inner products
+      if (both && !fold_s) dots((int*)nullptr, line);
+      update(false, false, folded, fold_s ? folded : chunks, 1, 1, sel ? (const double*)W.nsum : nullptr);
     } else {
-      update(0, h0, h0P, h0n, 0, 0, kDotChunk, (double2*)nullptr, 0, nullptr);
+      update(false, false, chunks, chunks, 0, 0, nullptr);
       // CGS2, second pass
-      dots((int*)nullptr);
-      if (long_vec)
-        hipLaunchKernelGGL(finish_partials_kernel, dim3((nvec + 3) / 4, B), dim3(256), 0, s, (const double2*)W.dpart, maxP,
-                           nvec, W.rv, W.hsum, live, W.idle, kDotChunk);
-      update(0, h0, h0P, h0n, 1, 1, kDotChunk, (double2*)nullptr, 0, nullptr);
+      dots((int*)nullptr, INT64_MAX);
+      if (long_vec) finish(W.dpart, maxP, kDotChunk);
+      update(false, false, chunks, chunks, 1, 1, nullptr);
     }
     if (long_vec)
       hipLaunchKernelGGL(finish_norm_kernel, dim3(B), dim3(256), 0, s, (const double*)W.npart, maxB, W.rv, W.nsum,
-                         live, W.idle, nsub, (const double2*)nullptr, 0, 0, 0);
+                         live, W.idle, (const double2*)nullptr, 0, 0, 0);
     const double* np = long_vec ? W.nsum : W.npart;
-    const int npB = long_vec ? 1 : maxB, npE = long_vec ? 0 : 64 * nsub;
+    const int npB = long_vec ? 1 : maxB, npS = long_vec ? 1 : 0;
     // blocks of whole units (the preconditioner multiplies per unit)
     const int nthr = pre ? (256 / n_a) * n_a : 256;
     const int64_t nb_n = ceil_div((size_t)maxN, nthr);
@@ -1750,7 +1836,7 @@ struct GmresRun {
     const bool c64 = Z->near_dtype == R3M_C64;
 #define R3M_NORMALIZE(OT, MODE, XS)                                                                                  \
   hipLaunchKernelGGL((normalize_step_kernel<OT, MODE, VB, WB>), ngrid, dim3(nthr), glds, s, wv, V, W.rv, W.st, np, npB, \
-                     npE, W.H, W.g, W.cs, W.sn, m, j, tol, run_slot(j), W.wn, ut, live, W.Minv, batch->states, W.soff, \
+                     npS, line, W.H, W.g, W.cs, W.sn, m, j, tol, run_slot(j), W.wn, ut, live, W.Minv, batch->states, W.soff, \
                      n_a, n_states, XS, pu, W.idle, rl, B, nb_n, stage)
     if (ilu_r) {
       // V_{j+1}, then the next step's input M^-1 V_{j+1} by the colour solves
@@ -1763,8 +1849,8 @@ struct GmresRun {
       // RW rows per thread: blocks of RW times the units
       auto rows = [&](auto kern, int rw) {
         const int64_t nbr = ceil_div((size_t)maxN, (size_t)rw * nthr);
-        hipLaunchKernelGGL(kern, dim3(stride_grid(nbr * B)), dim3(nthr), glds, s, wv, V, W.rv, W.st, np, npB, npE,
-                           W.H, W.g, W.cs, W.sn, m, j, tol, run_slot(j), W.wn, ut, live, W.Minv, batch->states,
+        hipLaunchKernelGGL(kern, dim3(stride_grid(nbr * B)), dim3(nthr), glds, s, wv, V, W.rv, W.st, np, npB, npS,
+                           line, W.H, W.g, W.cs, W.sn, m, j, tol, run_slot(j), W.wn, ut, live, W.Minv, batch->states,
                            W.soff, n_a, n_states, (float*)W.xs, pu, W.idle, rl, B, nbr, stage);
       };
       if (n_a % 4 == 0)
@@ -2085,11 +2171,13 @@ int r3m_gmres_solve(r3m_ctx ctx, const r3m_store* Z, const r3m_store* Z64,
     run.Zsolve = Z;
     run.ut = (int64_t)bd.total_units * n_a;
     run.maxN = 0;
+    run.minN = INT64_MAX;
     std::vector<RhsVec> rv(bd.B);
     std::vector<int64_t> soff(bd.B);
     for (int b = 0; b < bd.B; ++b) {
       rv[b] = RhsVec{bd.unit_off[b] * n_a, bd.n_units[b] * n_a};
       run.maxN = std::max(run.maxN, rv[b].N);
+      run.minN = std::min(run.minN, rv[b].N);
       soff[b] = batch->state_off[b];
     }
     run.maxP = (int)((run.maxN + kDotChunk - 1) / kDotChunk);
