@@ -277,6 +277,9 @@ int32_t r3m_matvec_groups(r3m_ctx ctx, const r3m_store* Z, const r3m_batch* batc
  * R3M_PLAN_SPEC_TWO_PASS when the retrieval transforms run as separate row
  * and column passes through HBM although the fused 2-D transform (complex64
  * grids of at most 16,384 points, one grid per workgroup in LDS) applies.
+ * Wide batches of shape 6 that fill the chip (from 49 right-hand sides, n a
+ * multiple of 16) run as a streamed kernel with one workgroup order: bits 4-11
+ * and 13-14 then have no effect, and the autotuner leaves them at the default.
  * The spectral autotuner runs on the first r3m_retrieved_matvec or
  * r3m_gmres_solve of the pair.  Every matrix-core shape and order gives the
  * same bits; the vector-unit shape and the transform form differ by FP32

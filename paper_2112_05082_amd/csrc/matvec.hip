@@ -2117,11 +2117,13 @@ int tuned_spectral(r3m_ctx ctx, const r3m_store* Z, const BatchDesc& bd, const u
     // the other workgroup order of the full batch: the shape's default
     // threshold orders RHS tile first from spec_default_rf tiles on, so from
     // there the alternative is the contiguous order at every count, below it
-    // RHS tile first from the batch's own tile count
+    // RHS tile first from the batch's own tile count (the streamed kernel has
+    // one order)
     const int n_bt = (bd.B + 15) / 16;
     std::sort(mfma.begin(), mfma.end());
     for (size_t i = 0; i < mfma.size() && i < 2 && n_bt > 1; ++i) {
       const int k = mfma[i].second;
+      if (spectral_streams(Z, bd.B, k)) continue;
       const int other = spec_plan(k, n_bt >= spec_default_rf(k) ? 255 : n_bt);
       const float ms = time_plan(other);
       if (ms < 0.97f * best_ms) {

@@ -49,6 +49,9 @@ int spectral_default_plan(const r3m_store* Z, int B);
 bool spectral_plan_valid(const r3m_store* Z, int plan);
 // the store's retrieval transforms can run fused (complex64 grids that fit LDS)
 bool spectral_fused_transforms(const r3m_store* Z);
+// the shape's product of B right-hand sides is the streamed kernel, which has
+// one workgroup order (the plan's order bits do not act)
+bool spectral_streams(const r3m_store* Z, int B, int shape);
 int choose_chunks(const BatchDesc& bd, int max_chunks);
 // largest displacement-group count the autotuner may pick (workspaces are sized for it)
 int max_groups(const BatchDesc& bd);

@@ -1535,6 +1535,7 @@ void launch_product_mfma(const C2<T>* Zh, const C2<T>* X, C2<T>* Y, int n, int64
   R3M_CHECK_HIP(hipGetLastError());
 }
 
+constexpr int kStreamShape = 6;  // its wide batches run the streamed kernel
 constexpr int kStreamWgs = 256;  // one per CU
 // Wide batches on stores whose rows fill 16-row tiles; the lanes' offsets in
 // the grids of 16 rows or right-hand sides take 31 bits.  Below four RHS tiles
@@ -1612,7 +1613,7 @@ void product(const C2<T>* Zh, const C2<T>* X, C2<T>* Y, int n, int64_t G2, int B
       case 3: R3M_MATRIX(2, 8, 1);
       case 4: R3M_MATRIX(4, 4, 1);
       case 5: R3M_MATRIX(1, 8, 1);
-      case 6:
+      case kStreamShape:
         if (product_streams(n, G2, B, tr)) return launch_product_stream(Zh, X, Y, n, G2, B, s, live, idle, tl);
         R3M_MATRIX(2, 4, 2);
       case 7: R3M_MATRIX(1, 8, 2);
@@ -1873,6 +1874,11 @@ bool spectral_plan_valid(const r3m_store* Z, int plan) {
 bool spectral_fused_transforms(const r3m_store* Z) {
   return Z->far_dtype == R3M_SPEC_C64 &&
          fft2_fits(ilog2(next_pow2(2 * Z->Dx + 1)), ilog2(next_pow2(2 * Z->Dy + 1)));
+}
+
+bool spectral_streams(const r3m_store* Z, int B, int shape) {
+  const int64_t G2 = (int64_t)next_pow2(2 * Z->Dx + 1) * next_pow2(2 * Z->Dy + 1);
+  return Z->far_dtype == R3M_SPEC_C64 && shape == kStreamShape && product_streams(Z->n, G2, B, false);
 }
 
 size_t relaxed_work_bytes(const BatchDesc& bd, const r3m_store* Z) { return spectral_work_bytes(bd, Z); }

@@ -68,3 +68,33 @@ def test_solve_with_shrinking_list():
     assert len(set(out[0][1])) >= 4 and out[0][1] == out[1][1]
     assert torch.equal(out[0][0], out[1][0])
     ctx.close()
+
+
+def test_tuned_plan_of_a_streamed_batch():
+    """The streamed kernel has one workgroup order: the tuner does not choose
+    between two of them, and pinned order bits change nothing."""
+    from paper_2112_05082_amd import r3m
+    ctx = r3m.Context(0)
+    n, D, B, L = 80, 31, 128, 4
+    g = torch.Generator(DEV).manual_seed(B)
+    spec = torch.randn(r3m.spectral_bytes(n, D, D, r3m.SPEC_C64) // 4, dtype=torch.float32, device=DEV, generator=g)
+    near = torch.randn((1, n, n), dtype=torch.complex64, device=DEV, generator=g)
+    store = r3m.Store(n, 2, D, D, 0, r3m.C64, near, r3m.SPEC_C64, spec)
+    books = [np.random.default_rng(b).integers(0, 2, L * L).astype(np.uint8) for b in range(B)]
+    x = torch.randn(B * L * L * 40, dtype=torch.complex64, device=DEV, generator=g)
+    out = []
+    for plan in (None, r3m.spec_plan(6, 64), r3m.spec_plan(6, 1), r3m.spec_plan(6, 255, kt_groups=2)):
+        batch = r3m.Batch.from_codebooks(books, [L] * B, DEV)
+        if plan is not None:
+            r3m.matvec_set_plan(ctx, store, batch, plan)
+        work = torch.empty(r3m.matvec_work_bytes(ctx, store, batch, r3m.C64), dtype=torch.uint8, device=DEV)
+        y = torch.zeros_like(x)
+        r3m.r3m_retrieved_matvec(ctx, store, batch, r3m.C64, x, y, work)
+        got = r3m.matvec_plan(ctx, store, batch)
+        if plan is None and got & 15 == 6:
+            assert (got >> 4) & 255 == 64
+        if plan is not None:
+            assert got == plan
+            out.append(y)
+    assert all(torch.equal(y, out[0]) for y in out[1:])
+    ctx.close()
