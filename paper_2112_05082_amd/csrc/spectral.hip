@@ -264,6 +264,7 @@ struct FftArgs {
   int macro_plain;  // kInvRows with wts: write y~ itself (the macro product Z P(w) x), no weights
   const int* live;
   const int* idle;  // per right-hand side (nullable): lines of b with idle[b] != 0 are left alone
+  int64_t wg0;      // first workgroup of this launch (see max_workgroups)
 };
 
 template <typename T>
@@ -297,13 +298,13 @@ __global__ void __launch_bounds__(256) fft_kernel(FftArgs<T> A) {
   int lig0;    // its line within the grid; line li is lig0 (chan) or lig0 + li
   if (chan) {
     const int ncg = (A.n + lpw - 1) >> A.lg_lpw;
-    const int64_t id = blockIdx.x;
+    const int64_t id = A.wg0 + blockIdx.x;
     const int cg = (int)(id % ncg);
     const int64_t rest = id / ncg;
     lig0 = (int)(rest & ((1 << A.lg_lpg) - 1));
     g0 = (rest >> A.lg_lpg) * A.n + ((int64_t)cg << A.lg_lpw);
   } else {
-    const int64_t l0 = (int64_t)blockIdx.x << A.lg_lpw;
+    const int64_t l0 = (A.wg0 + blockIdx.x) << A.lg_lpw;
     g0 = l0 >> A.lg_lpg;
     lig0 = (int)(l0 & ((1 << A.lg_lpg) - 1));
   }
@@ -478,8 +479,11 @@ void fft_pass(FftArgs<T> A, int lgGx, int lgGy, int64_t n_grids, hipStream_t s) 
   }
   const int G = 1 << A.lgG;
   const size_t lds = ((size_t)((size_t)1 << A.lg_lpw) * (G + (G >> 4) + 1) + G) * sizeof(C2<T>);
-  hipLaunchKernelGGL((fft_kernel<T, MODE, VT>), dim3((unsigned)n_wg), dim3(256), lds, s, A);
-  R3M_CHECK_HIP(hipGetLastError());
+  const int64_t most = max_workgroups(256);
+  for (A.wg0 = 0; A.wg0 < n_wg; A.wg0 += most) {
+    hipLaunchKernelGGL((fft_kernel<T, MODE, VT>), dim3((unsigned)std::min(most, n_wg - A.wg0)), dim3(256), lds, s, A);
+    R3M_CHECK_HIP(hipGetLastError());
+  }
 }
 
 // ----------------------------------------------------- fused 2-D transforms

@@ -58,3 +58,31 @@ def test_rcs_of_more_workgroups_than_one_launch_takes():
         ref = I[b:b + 512].abs().square()[:, None] * one[None, :]
         assert bool(((sigma[b:b + 512] - ref).abs() <= 1e-12 * ref).all()), b
     ctx.close()
+
+
+def test_line_transforms_of_more_workgroups_than_one_launch_takes():
+    """83 bases (odd: one line to a workgroup) x 128 rows x 1,600 right-hand
+    sides: 16,998,400 workgroups of 256 threads a row pass."""
+    from paper_2112_05082_amd import r3m
+    dev, n, D, B, L = "cuda:0", 83, 63, 1600, 2
+    ctx = r3m.Context(0)
+    g = torch.Generator(dev).manual_seed(1)
+    spec = torch.randn(r3m.spectral_bytes(n, D, D, r3m.SPEC_C128) // 8, dtype=torch.float64, device=dev, generator=g)
+    near = torch.randn((1, n, n), dtype=torch.complex128, device=dev, generator=g)
+    store = r3m.Store(n, 2, D, D, 0, r3m.C128, near, r3m.SPEC_C128, spec,
+                      common_ext=torch.tensor([0, 1, 2], dtype=torch.int32, device=dev))
+    books = [np.random.default_rng(b).integers(0, 2, L * L).astype(np.uint8) for b in range(B)]
+    x = torch.randn((B, L * L * 43), dtype=torch.complex128, device=dev, generator=g)
+
+    def product(first, count):
+        batch = r3m.Batch.from_codebooks(books[first:first + count], [L] * count, dev)
+        xs = x[first:first + count].contiguous()
+        work = torch.empty(r3m.matvec_work_bytes(ctx, store, batch, r3m.C128), dtype=torch.uint8, device=dev)
+        y = torch.zeros_like(xs)
+        r3m.r3m_retrieved_matvec(ctx, store, batch, r3m.C128, xs, y, work)
+        return y
+
+    y = product(0, B)
+    for first in (0, 800, 1579, 1592):  # complex128 products have the same bits at every width
+        assert torch.equal(y[first:first + 8], product(first, 8)), first
+    ctx.close()
