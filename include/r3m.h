@@ -246,7 +246,12 @@ size_t r3m_matvec_work_bytes(r3m_ctx ctx, const r3m_store* Z, const r3m_batch* b
  * basis range of state s.  Far blocks use U (V^H x).  Vectors are C128 or C64
  * (vec_dtype), accumulation is in the store's precision (FP64 for a C128
  * store, FP32 otherwise).  The sum over displacements is reduced in a fixed
- * order (bitwise reproducible run to run).  work: r3m_matvec_work_bytes.
+ * order (bitwise reproducible run to run).  Products on complex128 spectra
+ * have the same bits at every batch width; on the other stores the kernel or
+ * the split of the sum follows the batch (on all-dense ones its arrays and
+ * their unit pairs), so a right-hand side may differ by rounding from the same
+ * one in another batch.  Stores take 40 or 64 bases a state.  work:
+ * r3m_matvec_work_bytes.
  * Every state byte must be < n_states: the call checks them on the device
  * (unless R3M_BATCH_INDEX_READY) and r3m_ctx_check reports a violation. */
 int r3m_retrieved_matvec(r3m_ctx ctx, const r3m_store* Z, const r3m_batch* batch,
@@ -460,9 +465,14 @@ size_t r3m_gmres_work_bytes(r3m_ctx ctx, const r3m_store* Z, const r3m_store* Z6
  * FP64, convergence flags on the
  * device.  Blocks of Arnoldi steps run as HIP graphs captured once per
  * (store, batch, workspace, m) and replayed on a context-owned stream that is
- * ordered after `stream`; the call returns with `stream` ordered after it.  The matvec runs in the precision of Z.  If Z64 (a C128 store of the
- * same matrix) is given and opts->refine_tol > 0, an outer FP64 iterative
+ * ordered after `stream`; the call returns with `stream` ordered after it.
+ * The matvec runs in the precision of Z.  If Z64 (a C128 store of the same
+ * matrix) is given and opts->refine_tol > 0, an outer FP64 iterative
  * refinement computes r = b - Z64 x and solves Z d = r with the inner GMRES.
+ * Where the matvec's bits do not depend on the batch, neither do those of a
+ * solve in a batch whose vectors all have at most 65,536 entries (beside a
+ * longer one the shorter ones take its Gram-Schmidt form, with the selective
+ * repetition).
  * rep_host[B] is written; returns R3M_ERR_NOT_CONVERGED if any RHS missed the
  * tolerance (x still holds the last iterate).  Synchronises the stream.
  * Stores with shared (connected-geometry) bases: vectors in the store's
