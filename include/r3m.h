@@ -250,8 +250,8 @@ size_t r3m_matvec_work_bytes(r3m_ctx ctx, const r3m_store* Z, const r3m_batch* b
  * have the same bits at every batch width; on the other stores the kernel or
  * the split of the sum follows the batch (on all-dense ones its arrays and
  * their unit pairs), so a right-hand side may differ by rounding from the same
- * one in another batch.  Stores take 40 or 64 bases a state.  work:
- * r3m_matvec_work_bytes.
+ * one in another batch.  Stores take 40 bases a state, spectral and all-dense
+ * ones also 64 (R3M_ERR_UNSUPPORTED otherwise).  work: r3m_matvec_work_bytes.
  * Every state byte must be < n_states: the call checks them on the device
  * (unless R3M_BATCH_INDEX_READY) and r3m_ctx_check reports a violation. */
 int r3m_retrieved_matvec(r3m_ctx ctx, const r3m_store* Z, const r3m_batch* batch,
