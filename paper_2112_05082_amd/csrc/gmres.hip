@@ -691,8 +691,6 @@ gs_update_kernel(const VB* __restrict__ V, WB* __restrict__ w, const RhsVec* __r
 // stay in registers, each wave sums conj(V_i) w over its lanes
 // (wave_transpose_sum) and the block adds the waves in a fixed order into
 // partial2[b][i][block].  Same arguments and outputs as gs_update_kernel.
-// skip (nullable; a second pass, mode 1): the pass leaves w, its norm parts and
-// H alone for every RHS with skip[b] != 0 (finish_norm_kernel).
 template <int NV, typename VB, typename WB>
 __device__ __forceinline__ void gs_element_block(const VB* __restrict__ V, WB* __restrict__ w, const RhsVec r, int b,
                                                  int64_t blk, const RhsState* __restrict__ st, const GsSource src,
@@ -791,6 +789,8 @@ __device__ __forceinline__ void gs_element_block(const VB* __restrict__ V, WB* _
   }
 }
 
+// skip (nullable; a second pass, mode 1): the pass leaves w, its norm parts and
+// H alone for every RHS with skip[b] != 0 (finish_norm_kernel).
 template <int NV, typename VB, typename WB>
 __global__ void __launch_bounds__(256, NV == 20 ? 4 : 1)
 gs_update_el_kernel(const VB* __restrict__ V, WB* __restrict__ w, const RhsVec* __restrict__ rv,
